@@ -188,6 +188,11 @@ typedef struct {
                             before the current item's stores; 0: one item per
                             workgroup */
   int unpack_nt_stores;  /* 1: unpacking stores with the non-temporal policy */
+  int rows_bl;           /* tile edge of exec and adjoint where the planner's tile (the fields
+                            above) has no rows of whole 16-byte chunks: they then run on
+                            tiles of this edge with 16-byte loads and stores at any element
+                            alignment; 0 where they run on the tile above (also after
+                            spinsum_plan_set_tile with a tile edge) */
 } spinsum_plan_info_t;
 
 /* Create a plan for Out = S_K(...S_1(In)) (Def. 3-4; in-place: Sec. 4.6.5).

@@ -26,8 +26,11 @@
 //   k_lds     one item per workgroup, loads straight into LDS
 //             (global_load_lds), 256/512/1024 threads -- the default;
 //   k_ldsp    persistent, two LDS buffers, next item's loads in flight;
+//   k_rows    one item per workgroup, tile rows that start on any element
+//             (extents whose rows are not whole 16-byte chunks), loads
+//             straight into LDS but for the ends of the rows;
 //   k_exec    one item per workgroup, loads through registers into padded
-//             LDS (rows that are not whole 16-byte chunks);
+//             LDS (by request);
 //   k_pipe    persistent, next item prefetched into registers;
 //   k_batched many tensors, one item of the cost-sorted list per workgroup;
 //   k_pair    index-pair form: one tile orbit of combined (partner, group)
@@ -1123,6 +1126,179 @@ __global__ void __launch_bounds__(kMaxThreads) k_lds(const ExecArgs<T> a) {
     flat_store<T, NTS>(a.out + cube0 * g.cube_elems, span, smem, shift);
   else
     store_item_lds<T, D, NTS>(g, od, whole, ntl, ragged, a.out + cube0 * g.cube_elems, lds);
+}
+
+// ---- tile rows of any alignment (k_rows) ----
+// A vector of 16 bytes that starts on any element.
+template <typename T>
+struct AnyVec;
+template <>
+struct AnyVec<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <>
+struct AnyVec<float> {
+  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+
+// Elements of a row of a tile with packed extents `ext`.
+template <int D>
+__device__ __forceinline__ int tile_row_elems(const Geom& g, int ext) {
+  return ((ext >> (8 * (D - 1))) & 255) * g.inner;
+}
+
+// Issue the loads of an item whose tile rows start on any element.  A row
+// takes vpr = ceil(bl * inner / VW) chunks of 16 bytes in LDS; its whole
+// chunks go global->LDS directly (the address of global_load_lds_dwordx4
+// needs no 16-byte alignment in the tensor, only in LDS), the fewer than VW
+// elements after them through registers, a wave per tile at a time.
+// Nothing outside the tile is read.
+template <typename T, int D>
+__device__ __forceinline__ void issue_rows_lds(const Geom& g, cptr<GroupDev> od, int ntl,
+                                               const T* src, unsigned char* lds_bytes) {
+  constexpr int VW = 16 / sizeof(T);
+  const uint32_t cpt = (uint32_t)g.rows * (uint32_t)g.vpr;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wave_bytes = (tid >> 6) * 1024u;
+  for (uint32_t c0 = 0; c0 < cpt; c0 += blockDim.x) {
+    int l[D];
+    chunk_coords<D, VW>(g, c0 + tid, l);
+    const int off = chunk_offset<D>(g, l);
+    int last[D];  // the chunk's last element
+#pragma unroll
+    for (int m = 0; m < D; ++m) last[m] = l[m];
+    last[D - 1] += VW - 1;
+    const bool in = c0 + tid < cpt;
+    for (int t = 0; t < ntl; ++t) {
+      const uint32_t lbyte = (uint32_t)(t * g.ts + (int)c0 * VW) * (uint32_t)sizeof(T) + wave_bytes;
+      if (in && chunk_inside<D>(last, od->tile_ext[t], g.inner))
+        load_lds16<false>((const void*)(src + od->tile_off[t] + off),
+                          (__attribute__((address_space(3))) void*)(lds_bytes + lbyte));
+    }
+  }
+  // the ends of the rows, kTailBatch (tile, 64 rows) units of a wave
+  // requested together
+  constexpr int kTailBatch = 4;
+  T* lds = reinterpret_cast<T*>(lds_bytes);
+  const int lane = (int)(tid & 63u);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const int nwaves = (int)(blockDim.x >> 6);
+  const int rblk = (g.rows + 63) >> 6;
+  for (int u0 = wave; u0 < ntl * rblk; u0 += nwaves * kTailBatch) {
+    T v[kTailBatch][VW - 1];
+    int lo[kTailBatch], cnt[kTailBatch];
+#pragma unroll
+    for (int b = 0; b < kTailBatch; ++b) {
+      const int u = u0 + b * nwaves;
+      cnt[b] = 0;
+      lo[b] = 0;
+      if (u < ntl * rblk) {
+        const int t = u / rblk;
+        const int row = (u - t * rblk) * 64 + lane;
+        const int ext = od->tile_ext[t];
+        const int len = tile_row_elems<D>(g, ext);
+        const int tail = len % VW;
+        int l[D];
+        chunk_coords<D, VW>(g, (uint32_t)row * (uint32_t)g.vpr, l);
+        if (row < g.rows && tail != 0 && chunk_inside<D>(l, ext, g.inner)) {
+          l[D - 1] = len - tail;
+          cnt[b] = tail;
+          lo[b] = t * g.ts + row * g.vpr * VW + l[D - 1];
+          const T* p = src + od->tile_off[t] + chunk_offset<D>(g, l);
+#pragma unroll
+          for (int k = 0; k < VW - 1; ++k)
+            if (k < tail) v[b][k] = p[k];
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < kTailBatch; ++b) {
+#pragma unroll
+      for (int k = 0; k < VW - 1; ++k)
+        if (k < cnt[b]) lds[lo[b] + k] = v[b][k];
+    }
+  }
+}
+
+// Store every tile of such an item: whole chunks with 16-byte stores at any
+// element alignment, the ends of the rows element by element.
+template <typename T, int D, bool NTS>
+__device__ __forceinline__ void store_rows_lds(const Geom& g, cptr<GroupDev> od, int ntl, T* dst,
+                                               const T* lds) {
+  constexpr int VW = 16 / sizeof(T);
+  typedef typename VecT<T, VW>::type V;
+  typedef typename AnyVec<T>::type U;
+  const uint32_t cpt = (uint32_t)g.rows * (uint32_t)g.vpr;
+  for (uint32_t c0 = 0; c0 < cpt; c0 += blockDim.x) {
+    const uint32_t c = c0 + threadIdx.x;
+    int l[D];
+    chunk_coords<D, VW>(g, c, l);
+    const int off = chunk_offset<D>(g, l);
+    const bool in = c < cpt;
+    for (int t = 0; t < ntl; ++t) {
+      const int ext = od->tile_ext[t];
+      if (!(in && chunk_inside<D>(l, ext, g.inner))) continue;
+      const int left = tile_row_elems<D>(g, ext) - l[D - 1];
+      const V val = *reinterpret_cast<const V*>(lds + t * g.ts + (int)c * VW);
+      T* p = dst + od->tile_off[t] + off;
+      if (left >= VW) {
+        const U any = val;
+        if constexpr (NTS)
+          __builtin_nontemporal_store(any, reinterpret_cast<U*>(p));
+        else
+          *reinterpret_cast<U*>(p) = any;
+      } else {
+#pragma unroll
+        for (int k = 0; k < VW - 1; ++k)
+          if (k < left) p[k] = val[k];
+      }
+    }
+  }
+}
+
+// One-shot, tile orbits whose rows start on any element (odd extents): the
+// direct-LDS kernel with issue_rows_lds and store_rows_lds.  The register
+// path moves one or two elements per lane there and is bound by its
+// instructions (33^3: about 180 G elements/s in FP64, 230 in FP32).  Bound
+// here by the L1's requests: a 64-byte row at any alignment takes 1.5 to 2
+// of them.  Against the register path, 2 x 134 M elements: 33^3 FP64 in
+// place 3.76 against 2.92 TB/s, 33^3 / 37^3 FP32 2.67 / 3.15 against 1.83 /
+// 1.63, 15^4 FP64 2.35 against 1.93, 15^4 FP32 2.05 against 1.22.
+// LDS: [tiles (lds_tile_bytes) | representatives (rep_total entries)].
+template <typename T, int D, bool CHAIN, bool NTS>
+__global__ void __launch_bounds__(kMaxThreads) k_rows(const ExecArgs<T> a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T* lds = reinterpret_cast<T*>(smem);
+  int64_t item;
+  if (a.xcd_per > 0)
+    item = (int64_t)(blockIdx.x & 7u) * a.xcd_per + (int64_t)(blockIdx.x >> 3);
+  else
+    item = blockIdx.x;
+  if (item >= a.nitems) return;
+  if (a.reverse) item = a.nitems - 1 - item;
+  const Geom& g = a.g;
+  int64_t cube0;
+  int orbit, ncub;
+  decode_item(g, item, &cube0, &orbit, &ncub);
+  const cptr<GroupDev> od = as_const(a.orbits + orbit);
+  const int ntl = od->ntiles;
+  const T* src = a.in + cube0 * g.cube_elems;
+  unsigned char* rep_lds = smem + a.lds_tile_bytes;
+  clear_terms_flag(a.sparse);
+  set_memory_priority();
+  issue_reps_lds(od, a.reps, rep_lds);
+  issue_rows_lds<T, D>(g, od, ntl, src, smem);
+  set_compute_priority();
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): everything is in LDS
+  __syncthreads();
+  const uint32_t* reps = reinterpret_cast<const uint32_t*>(rep_lds);
+  const bool bad = combine_item<T, D, CHAIN, true>(g, od, reps, as_const(a.coef), a.nstages, 1, lds);
+  if (item_needs_terms(a.sparse, bad)) {
+    redo_item<T, D, CHAIN, true>(g, od, reps, as_const(a.coef), a.nstages, 1, src, lds);
+    __syncthreads();
+  }
+  set_memory_priority();
+  store_rows_lds<T, D, NTS>(g, od, ntl, a.out + cube0 * g.cube_elems, lds);
 }
 
 // Index-pair form: one tile orbit {sigma . c} of one pair block per
@@ -2287,12 +2463,16 @@ const void* pipe_kernel(int vw) {
 
 // kind: 1 direct-LDS one-shot, 2 register-prefetch persistent (maxc = 8 or
 // 16), 3 register one-shot, 4 direct-LDS double-buffered persistent,
-// 5 index-pair form (direct-LDS one-shot)
+// 5 index-pair form (direct-LDS one-shot), 6 tile rows of any alignment
 template <typename T, int D>
 const void* pick_d(int kind, int vw, bool chain, bool nts, int maxc) {
   if (kind == 5) {
     if (chain) return nts ? (const void*)k_pair<T, D, true, true> : (const void*)k_pair<T, D, true, false>;
     return nts ? (const void*)k_pair<T, D, false, true> : (const void*)k_pair<T, D, false, false>;
+  }
+  if (kind == 6) {
+    if (chain) return nts ? (const void*)k_rows<T, D, true, true> : (const void*)k_rows<T, D, true, false>;
+    return nts ? (const void*)k_rows<T, D, false, true> : (const void*)k_rows<T, D, false, false>;
   }
   if (kind == 1) {
     if (chain) return nts ? (const void*)k_lds<T, D, true, true> : (const void*)k_lds<T, D, true, false>;

@@ -98,9 +98,17 @@ struct LaunchCfg {
 
 template <typename T>
 LaunchCfg exec_cfg(const spinsum_plan_s* P, bool chain) {
+  LaunchCfg c;
+  if (P->x_rows) {
+    const Tiling& Tx = P->Tx;
+    c.kind = kVariantAnyRows;
+    c.k = pick_kernel<T>(P->d, c.kind, Tx.vw, chain, Tx.nts != 0, 0);
+    c.shmem = ((size_t)Tx.lds_elems * sizeof(T) + 15) / 16 * 16 + (size_t)Tx.max_rep_cnt * 4;
+    c.threads = P->x_threads;
+    return c;
+  }
   const Tiling& Tl = P->T;
   const bool nts = Tl.nts != 0;
-  LaunchCfg c;
   int kind = P->tile.variant;
   if (!nts && kind == SPINSUM_VARIANT_REG_PIPELINE) kind = SPINSUM_VARIANT_REG_ONESHOT;
   const int maxc = (kind == SPINSUM_VARIANT_REG_PIPELINE) ? (Tl.chunks_per_thread <= 8 ? 8 : 16) : 0;
@@ -181,15 +189,15 @@ CoefSel stage_sel(const spinsum_plan_s* P, bool adjoint, int j) {
 template <typename T>
 spinsum_status launch_exec(spinsum_plan_s* P, const void* in, void* out, hipStream_t stream,
                            const CoefSel& sel) {
-  const Tiling& Tl = P->T;
+  const Tiling& Tl = P->x_rows ? P->Tx : P->T;
   if (Tl.nitems <= 0) return SPINSUM_OK;
   const T* coef = reinterpret_cast<const T*>(P->d_mats);
   ExecArgs<T> a;
   std::memset(&a, 0, sizeof(a));
   a.in = reinterpret_cast<const T*>(in);
   a.out = reinterpret_cast<T*>(out);
-  a.orbits = reinterpret_cast<const GroupDev*>(P->d_orbits);
-  a.reps = reinterpret_cast<const uint32_t*>(P->d_reps);
+  a.orbits = reinterpret_cast<const GroupDev*>(P->x_rows ? P->d_x_orbits : P->d_orbits);
+  a.reps = reinterpret_cast<const uint32_t*>(P->x_rows ? P->d_x_reps : P->d_reps);
   a.coef = coef + sel.offset;
   a.nstages = sel.nstages;
   a.sparse = sel.sparse;

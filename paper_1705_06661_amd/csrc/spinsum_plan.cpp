@@ -94,10 +94,12 @@ static int vw_for(int64_t n_row, int64_t bl_row, int vmax) {
 // LDS strides of a tile: the last group axis has stride `inner` (each group
 // position holds a run of inner spectator elements), rows padded by one
 // element when pad is set.
-static void lds_strides(int d, int bl, int pad, int inner, int32_t* lst, int32_t* ts) {
+// row > 0: every row takes that many elements instead (k_rows).
+static void lds_strides(int d, int bl, int pad, int inner, int32_t* lst, int32_t* ts,
+                        int row = 0) {
   lst[d - 1] = inner;
   for (int m = d - 2; m >= 0; --m) {
-    int64_t s = (int64_t)lst[m + 1] * bl;
+    int64_t s = (m == d - 2 && row > 0) ? row : (int64_t)lst[m + 1] * bl;
     if (pad && (s % 2) == 0) s += 1;
     lst[m] = (int32_t)s;
   }
@@ -374,6 +376,9 @@ spinsum_status build_tiling(const spinsum_plan_s& P, int n, int64_t ncubes,
   if (cube_elems * elem_size(P) >= (1ll << 31)) return SPINSUM_ERR_UNSUPPORTED;
   const int nb = (n + bl - 1) / bl;
   const int vw = vw_for((int64_t)n * inner, (int64_t)bl * inner, vmax);
+  // k_rows: in LDS every row starts on a 16-byte chunk
+  const bool any_rows = tile.variant == kVariantAnyRows && bl < n;
+  const int chunk = 16 / elem_size(P);
 
   Geom& g = T.g;
   g.cube_elems = cube_elems;
@@ -383,10 +388,11 @@ spinsum_status build_tiling(const spinsum_plan_s& P, int n, int64_t ncubes,
   g.cpw = cpw;
   for (int m = 0; m < kMaxD; ++m) g.gst[m] = 0;
   for (int m = 0; m < d; ++m) g.gst[m] = (int32_t)(ipow(n, d - 1 - m) * inner);
-  lds_strides(d, bl, pad, inner, g.lst, &g.ts);
+  g.vpr = any_rows ? (bl * inner + chunk - 1) / chunk : bl * inner / vw;
+  lds_strides(d, bl, any_rows ? 0 : pad, inner, g.lst, &g.ts, any_rows ? g.vpr * chunk : 0);
+  T.any_rows = any_rows ? 1 : 0;
   g.cube_lds = g.ts;
   g.rows = (int32_t)ipow(bl, d - 1);
-  g.vpr = bl * inner / vw;
   g.inner = inner;
   g.pad0 = 0;
   g.fd_vpr = make_fastdiv((uint32_t)g.vpr);
@@ -590,7 +596,8 @@ static spinsum_status hip_fail(spinsum_plan_s* P, hipError_t e) {
 void free_device(spinsum_plan_s* P) {
   void** ptrs[] = {&P->d_orbits,    &P->d_reps,        &P->d_mats,      &P->d_blocks,
                    &P->d_items,     &P->d_grad_part,   &P->d_cg_orbits, &P->d_cg_reps,
-                   &P->d_reps_lex,  &P->d_pk_orbits,   &P->d_pk_reps};
+                   &P->d_reps_lex,  &P->d_pk_orbits,   &P->d_pk_reps,   &P->d_x_orbits,
+                   &P->d_x_reps};
   for (void** p : ptrs) {
     if (*p) (void)hipFree(*p);
     *p = nullptr;
@@ -788,6 +795,65 @@ static void choose_unpack_tiling(spinsum_plan_s* P) {
   }
 }
 
+// The sum's tiles for k_rows where the planner's default is the register
+// path (no edge has rows of whole 16-byte chunks: odd extents above all).
+// k_rows loads and stores 16 bytes a lane at any element alignment, so the
+// edge follows the rule of the direct-LDS tiles, on the tile row alone: rows
+// of at least 32 bytes within 32 KiB of LDS an orbit, else within 64 KiB,
+// else of 16 bytes within 32 KiB (the 7^3 tiles of the register path: 33^3
+// FP64 3.16 TB/s in this kernel, 3.76 at 8^3; 37^3 FP32 2.54 at 9^3, 3.15 at
+// 8^3, 2.39 at 12^3).  Cached stores: neighbouring rows share lines, which
+// the L2 merges (37^3 FP32 out of place 3.10 against 1.51 TB/s
+// non-temporal; 33^3 FP64 3.77 against 3.65).
+static void choose_rows_tiling(spinsum_plan_s* P) {
+  P->x_rows = false;
+  if (P->pair || P->batched || P->ncubes <= 0 || P->elems <= 0 || P->n <= 0 ||
+      P->T.g.bl >= P->n || P->tile.variant != SPINSUM_VARIANT_REG_ONESHOT ||
+      (P->flags & SPINSUM_FLAG_NO_DIRECT_LDS) || (int64_t)P->T.vw * elem_size(*P) == 16)
+    return;
+  const int esz = elem_size(*P);
+  const int64_t budget = P->lds_limit - 512;
+  const int vmax = max_vector_width(*P, (int64_t)P->n * P->inner);
+  struct Pass {
+    int min_row;
+    int64_t cap;
+  };
+  const Pass passes[] = {{32, 32 * 1024}, {32, 64 * 1024}, {16, 32 * 1024}};
+  for (const Pass& ps : passes)
+    for (int bl = std::min(P->n - 1, 255); bl >= 1; --bl) {
+      const int64_t row = (int64_t)bl * P->inner * esz;
+      if (row < ps.min_row || row % 16 != 0) continue;
+      if (tile_lds_bytes(*P, P->n, bl, 1, 0) > std::min(ps.cap, budget)) continue;
+      // FP64 keeps the register tiles where these cover far more than the
+      // cube and those do not (21^4: 24^4 against 21^4 in full tiles, 2.00
+      // against 2.06 TB/s; 17^4, 1.5 times as much, 1.91 against 1.69)
+      auto cover = [&](int b) { return ipow((P->n + b - 1) / b * b, P->d); };
+      if (esz == 8 && cover(bl) * 5 > cover(P->T.g.bl) * 8) return;
+      spinsum_tile_t t{};
+      t.bl = bl;
+      t.cubes_per_wg = 1;
+      t.variant = kVariantAnyRows;
+      Tiling Tx;
+      if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tx) != SPINSUM_OK || !Tx.fits) continue;
+      auto per_cu_of = [&](const Tiling& X) {
+        const int64_t wg = (X.lds_elems * esz + 15) / 16 * 16 + (int64_t)X.max_rep_cnt * 4;
+        return std::max<int64_t>(1, P->lds_limit / std::max<int64_t>(1, wg));
+      };
+      if (per_cu_of(Tx) < 4) {  // as for the direct-LDS tiles (apply_tile)
+        t.item_tiles = Tx.max_orbit_tiles;
+        Tiling packed;
+        if (build_tiling(*P, P->n, P->ncubes, t, vmax, &packed) == SPINSUM_OK && packed.fits)
+          Tx = std::move(packed);
+      }
+      const int64_t per_cu = per_cu_of(Tx);
+      P->x_threads = per_cu >= 4 ? 256 : per_cu >= 2 ? 512 : 1024;
+      Tx.nts = (P->flags & SPINSUM_FLAG_NT_STORES) ? 1 : 0;
+      P->Tx = std::move(Tx);
+      P->x_rows = true;
+      return;
+    }
+}
+
 spinsum_status upload_tables(spinsum_plan_s* P) {
   free_device(P);
   P->cg_split = cgrad_split_ok(*P);
@@ -813,12 +879,22 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
     st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
     if (st != SPINSUM_OK) return st;
   } else if (!P->batched) {
-    st = upload(P, &P->d_orbits, P->T.groups.data(), P->T.groups.size());
-    if (st != SPINSUM_OK) return st;
-    st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
-    if (st != SPINSUM_OK) return st;
-    if (!P->T.reps_lex.empty()) {
-      st = upload(P, &P->d_reps_lex, P->T.reps_lex.data(), P->T.reps_lex.size());
+    // (with x_rows nothing runs on T: the coefficient gradient and packing
+    // refuse rows that are not whole 16-byte chunks)
+    if (!P->x_rows) {
+      st = upload(P, &P->d_orbits, P->T.groups.data(), P->T.groups.size());
+      if (st != SPINSUM_OK) return st;
+      st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
+      if (st != SPINSUM_OK) return st;
+      if (!P->T.reps_lex.empty()) {
+        st = upload(P, &P->d_reps_lex, P->T.reps_lex.data(), P->T.reps_lex.size());
+        if (st != SPINSUM_OK) return st;
+      }
+    }
+    if (P->x_rows) {
+      st = upload(P, &P->d_x_orbits, P->Tx.groups.data(), P->Tx.groups.size());
+      if (st != SPINSUM_OK) return st;
+      st = upload(P, &P->d_x_reps, P->Tx.reps.data(), P->Tx.reps.size());
       if (st != SPINSUM_OK) return st;
     }
     std::vector<double> part((size_t)kGradSlots * P->G.df, 0.0);
@@ -1267,6 +1343,8 @@ static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req) {
   T.ntl = choose_ntl(*P, T);
   P->tile = t;
   P->T = std::move(T);
+  P->x_rows = false;
+  if (chosen) choose_rows_tiling(P);
   return SPINSUM_OK;
 }
 
@@ -1634,6 +1712,9 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
   Tiling keepT = P->T;
   const PairGeom keep_pg = P->pg;
   const std::vector<uint64_t> keep_orbits = P->pair_orbits;
+  const Tiling keep_tx = P->Tx;
+  const bool keep_rows = P->x_rows;
+  const int keep_x_threads = P->x_threads;
   spinsum_status st = apply_tile(P, tile);
   if (st == SPINSUM_OK) st = upload_tables(P);
   if (st != SPINSUM_OK) {
@@ -1641,6 +1722,9 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
     P->T = keepT;
     P->pg = keep_pg;
     P->pair_orbits = keep_orbits;
+    P->Tx = keep_tx;
+    P->x_rows = keep_rows;
+    P->x_threads = keep_x_threads;
     spinsum_status st2 = upload_tables(P);
     (void)st2;
   }
@@ -1697,6 +1781,7 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
       (!P->batched && !P->pair && (P->pk_own ? P->Tu.nts : P->T.nts) != 0) ? 1 : 0;
   info->unpack_persistent = (!P->batched && !P->pair && P->pk_own && P->pk_persist &&
                         !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 1 : 0;
+  info->rows_bl = P->x_rows ? P->Tx.g.bl : 0;
   info->batch_item_bytes = P->batched ? P->batch_item_bytes : 0;
   info->batch_persistent = P->batched ? P->batch_persistent : 0;
   if (!P->batched) {
@@ -1816,9 +1901,23 @@ static bool emulate_item(const Tiling& T, const GroupDev& gd, int ncub, std::str
     int lo = 0;
     if (!chunk_addr<D, VW>(g, c, gd.ntiles, gd.tile_off, gd.tile_ext, gd.ragged != 0, &go, &lo))
       continue;
-    if (go < 0 || go + VW > span || (go % VW) != 0) { *why = "global chunk out of bounds"; return false; }
-    if (lo < 0 || lo + VW > T.lds_elems) { *why = "LDS chunk out of bounds"; return false; }
-    for (int k = 0; k < VW; ++k) {
+    // k_rows: a row's last chunk holds what is left of the row
+    int nel = VW;
+    if (T.any_rows) {
+      const int s = (int)((c / (uint32_t)g.vpr) / (uint32_t)g.rows);
+      const int col = (int)(c % (uint32_t)g.vpr) * VW;
+      nel = std::min(VW, ((gd.tile_ext[s] >> (8 * (d - 1))) & 255) * g.inner - col);
+      if (nel <= 0) continue;
+    }
+    if (go < 0 || go + nel > span || (!T.any_rows && (go % VW) != 0)) {
+      *why = "global chunk out of bounds";
+      return false;
+    }
+    if (lo < 0 || lo + VW > T.lds_elems || (T.any_rows && (lo % VW) != 0)) {
+      *why = "LDS chunk out of bounds";
+      return false;
+    }
+    for (int k = 0; k < nel; ++k) {
       if (lds_of[lo + k] != -1) { *why = "LDS slot written twice"; return false; }
       lds_of[lo + k] = go + k;
       loaded[go + k] += 1;
@@ -1873,8 +1972,9 @@ static bool emulate_all(const Tiling& T, std::string* why, bool flat, int esz) {
     for (int nc : ncubs) {
       bool ok = false;
       if (flat && !emulate_flat<D>(T, gd, nc, esz, why)) return false;
-      if (T.vw == 4) ok = emulate_item<D, 4>(T, gd, nc, why);
-      else if (T.vw == 2) ok = emulate_item<D, 2>(T, gd, nc, why);
+      const int vw = T.any_rows ? 16 / esz : T.vw;
+      if (vw == 4) ok = emulate_item<D, 4>(T, gd, nc, why);
+      else if (vw == 2) ok = emulate_item<D, 2>(T, gd, nc, why);
       else ok = emulate_item<D, 1>(T, gd, nc, why);
       if (!ok) return false;
     }
@@ -1983,31 +2083,11 @@ static bool check_pair(const spinsum_plan_s& P, std::string* why) {
   return true;
 }
 
-extern "C" spinsum_status spinsum_plan_check_ownership(spinsum_plan_t P, int block, const char** why) {
-  static thread_local std::string msg;
-  auto fail = [&](const std::string& m) {
-    msg = m;
-    if (why) *why = msg.c_str();
-    return SPINSUM_ERR_INVALID_ARG;
-  };
-  if (why) *why = "";
-  if (P == nullptr) return SPINSUM_ERR_INVALID_ARG;
-  if (P->sub) return spinsum_plan_check_ownership(P->sub, block, why);
-  if (block < 0 || block >= P->nblocks) return SPINSUM_ERR_INVALID_ARG;
-  const Tiling& T = P->batched ? P->btil[block] : P->T;
+// The ownership and address checks of spinsum_plan_check_ownership for one
+// tiling of the plan ("" when it holds).
+static std::string check_tiling(const spinsum_plan_s& P, const Tiling& T) {
   const Geom& g = T.g;
-  if (g.n <= 0 || g.ncubes <= 0) return SPINSUM_OK;
-  if (P->pair) {
-    std::string w;
-    const int vw = 16 / elem_size(*P);
-    bool ok;
-    if (P->d == 2) ok = (vw == 2) ? check_pair<2, 2>(*P, &w) : check_pair<2, 4>(*P, &w);
-    else if (P->d == 3) ok = (vw == 2) ? check_pair<3, 2>(*P, &w) : check_pair<3, 4>(*P, &w);
-    else ok = (vw == 2) ? check_pair<4, 2>(*P, &w) : check_pair<4, 4>(*P, &w);
-    if (!ok) return fail(w);
-    return SPINSUM_OK;
-  }
-  const int d = P->d, df = P->G.df, n = g.n, bl = g.bl;
+  const int d = P.d, df = P.G.df, n = g.n, bl = g.bl;
   // every orbit of the cube belongs to exactly one work item
   std::vector<int> orbit_in(T.orbits.size(), 0);
   std::vector<int64_t> owner((size_t)g.cube_elems, -1);
@@ -2025,56 +2105,87 @@ extern "C" spinsum_status spinsum_plan_check_ownership(spinsum_plan_t P, int blo
         for (int m = 0; m < d; ++m) same = same && T.orbits[o].B[m] == B[m];
         if (same) match = (int)o;
       }
-      if (match < 0) return fail("work item holds an unknown orbit");
+      if (match < 0) return "work item holds an unknown orbit";
       orbit_in[match] += 1;
       const OrbitHost& oh = T.orbits[match];
       tiles += oh.ntiles;
       for (int r = 0; r < df; ++r) {
         // the tile recorded for sigma must be sigma . B
         int s = gd.slot_base[k][r] / g.ts;
-        if (s < 0 || s >= gd.ntiles || gd.slot_base[k][r] != s * g.ts) return fail("bad slot");
+        if (s < 0 || s >= gd.ntiles || gd.slot_base[k][r] != s * g.ts) return "bad slot";
         int64_t off = 0;
-        for (int m = 0; m < d; ++m) off += (int64_t)B[P->G.p[r][m]] * bl * g.gst[m];
-        if (off != gd.tile_off[s]) return fail("slot table does not match sigma . B");
+        for (int m = 0; m < d; ++m) off += (int64_t)B[P.G.p[r][m]] * bl * g.gst[m];
+        if (off != gd.tile_off[s]) return "slot table does not match sigma . B";
       }
       for (int i = 0; i < gd.rep_cnt[k]; ++i) {
         uint32_t pk = T.reps[gd.rep_off[k] + i];
         int x[kMaxD];
         for (int m = 0; m < d; ++m) {
           int l = (pk >> (8 * m)) & 255;
-          if (l >= std::min(bl, n - B[m] * bl)) return fail("representative outside its tile");
+          if (l >= std::min(bl, n - B[m] * bl)) return "representative outside its tile";
           x[m] = B[m] * bl + l;
         }
         for (int si = 0; si < g.inner; ++si) {
           const int64_t id = next_id++;
           for (int r = 0; r < df; ++r) {
             int64_t e = si;
-            for (int m = 0; m < d; ++m) e += (int64_t)x[P->G.p[r][m]] * g.gst[m];
-            if (owner[e] != -1 && owner[e] != id) return fail("element owned twice");
+            for (int m = 0; m < d; ++m) e += (int64_t)x[P.G.p[r][m]] * g.gst[m];
+            if (owner[e] != -1 && owner[e] != id) return "element owned twice";
             owner[e] = id;
           }
         }
       }
     }
-    if (tiles != gd.ntiles) return fail("work item tile count");
+    if (tiles != gd.ntiles) return "work item tile count";
   }
   for (int c : orbit_in)
-    if (c != 1) return fail("tile orbit not in exactly one work item");
+    if (c != 1) return "tile orbit not in exactly one work item";
   for (int64_t e = 0; e < g.cube_elems; ++e)
-    if (owner[e] == -1) return fail("element not owned");
+    if (owner[e] == -1) return "element not owned";
   std::string w;
   // whole cubes are also copied as one contiguous run by the direct-LDS
   // kernels (single tensors) and by the batched kernel
   const bool flat = (g.bl == g.n) &&
-                    (P->batched || P->tile.variant == SPINSUM_VARIANT_DIRECT_LDS);
-  const int esz = elem_size(*P);
+                    (P.batched || P.tile.variant == SPINSUM_VARIANT_DIRECT_LDS);
+  const int esz = elem_size(P);
   bool ok = (d == 2)   ? emulate_all<2>(T, &w, flat, esz)
             : (d == 3) ? emulate_all<3>(T, &w, flat, esz)
                        : emulate_all<4>(T, &w, flat, esz);
-  if (!ok) return fail(w);
-  return SPINSUM_OK;
+  if (!ok) return w;
+  return "";
 }
 
+extern "C" spinsum_status spinsum_plan_check_ownership(spinsum_plan_t P, int block, const char** why) {
+  static thread_local std::string msg;
+  auto fail = [&](const std::string& m) {
+    msg = m;
+    if (why) *why = msg.c_str();
+    return SPINSUM_ERR_INVALID_ARG;
+  };
+  if (why) *why = "";
+  if (P == nullptr) return SPINSUM_ERR_INVALID_ARG;
+  if (P->sub) return spinsum_plan_check_ownership(P->sub, block, why);
+  if (block < 0 || block >= P->nblocks) return SPINSUM_ERR_INVALID_ARG;
+  const Tiling& T0 = P->batched ? P->btil[block] : P->T;
+  if (T0.g.n <= 0 || T0.g.ncubes <= 0) return SPINSUM_OK;
+  if (P->pair) {
+    std::string w;
+    const int vw = 16 / elem_size(*P);
+    bool ok;
+    if (P->d == 2) ok = (vw == 2) ? check_pair<2, 2>(*P, &w) : check_pair<2, 4>(*P, &w);
+    else if (P->d == 3) ok = (vw == 2) ? check_pair<3, 2>(*P, &w) : check_pair<3, 4>(*P, &w);
+    else ok = (vw == 2) ? check_pair<4, 2>(*P, &w) : check_pair<4, 4>(*P, &w);
+    if (!ok) return fail(w);
+    return SPINSUM_OK;
+  }
+  const std::string bad = check_tiling(*P, T0);
+  if (!bad.empty()) return fail(bad);
+  if (P->x_rows) {  // the tiles the sum runs on
+    const std::string bad_rows = check_tiling(*P, P->Tx);
+    if (!bad_rows.empty()) return fail(bad_rows);
+  }
+  return SPINSUM_OK;
+}
 extern "C" void spinsum_plan_destroy(spinsum_plan_t P) {
   if (!P) return;
   if (P->sub) spinsum_plan_destroy(P->sub);

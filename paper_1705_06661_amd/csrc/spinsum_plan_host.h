@@ -47,6 +47,7 @@ struct Tiling {
   int max_rep_cnt = 0;        // representatives of the largest work item
   int nts = 1;                // non-temporal stores
   int ntl = 0;                // non-temporal tile loads (items own whole lines)
+  int any_rows = 0;           // k_rows: rows start on any element, 16-byte chunks in LDS
   std::vector<OrbitHost> orbits;
   std::vector<GroupDev> groups;
   std::vector<uint32_t> reps;
@@ -97,6 +98,12 @@ struct spinsum_plan_s {
   // tile's chunks in one pass of the workgroup, no inner runs, d <= 3
   // (decided with the tables, upload_tables)
   bool cg_split = false;
+  // The sum's own tiling for k_rows (see choose_rows_tiling): where the plan's
+  // default tiles have no rows of whole 16-byte chunks, exec and adjoint run
+  // on these tiles instead of T's register tiles
+  spinsum::Tiling Tx;
+  bool x_rows = false;
+  int x_threads = 256;
   // unpacking's own tiling where it differs from T (pk_own): the largest
   // items that fit a CU (see build_unpack_tiling), with their workgroup size
   spinsum::Tiling Tu;
@@ -148,12 +155,18 @@ struct spinsum_plan_s {
   void* d_cg_reps = nullptr;
   void* d_pk_orbits = nullptr;  // Tu.groups, Tu.reps (pk_own)
   void* d_pk_reps = nullptr;
+  void* d_x_orbits = nullptr;  // Tx.groups, Tx.reps (x_rows)
+  void* d_x_reps = nullptr;
   int last_hip_error = 0;
   int occ_blocks = 1;  // workgroups per CU of the persistent exec kernel (cache_occupancy)
   std::string why;
 };
 
 namespace spinsum {
+// Tile variant of Tiling::any_rows (k_rows): chosen by the planner for Tx,
+// never requested.
+constexpr int kVariantAnyRows = 6;
+
 // Implemented in spinsum_plan.cpp
 spinsum_status build_tiling(const spinsum_plan_s& P, int n, int64_t ncubes,
                             const spinsum_tile_t& tile, int vw, Tiling* out);

@@ -241,6 +241,9 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
     if (2 * mo <= kMaxGroupTiles) shapes.push_back({bl, 1, 256, 0, 0, 2 * mo});
   }
   std::vector<spinsum_tile_t> cands;
+  // the planner's own choice first: where it runs on tiles that no request
+  // names (spinsum_plan_info_t.rows_bl), winning keeps it
+  if (P->x_rows) cands.push_back(spinsum_tile_t{0, 1, 0, 1, 0, 0});
   for (const spinsum_tile_t& sh : shapes) {
     spinsum_tile_t t = sh;
     t.lds_pad = 0;
@@ -287,7 +290,7 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
     if (!ok) continue;
     if (!have || ms_min < win_ms) {
       have = true;
-      win = P->tile;
+      win = t.bl > 0 ? P->tile : t;
       win_ms = ms_min;
     }
   }
@@ -297,6 +300,7 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
   if (st != SPINSUM_OK) return st;
   if (best) *best = P->tile;
   if (best_ms) *best_ms = have ? win_ms : 0.0f;
-  if (have && cache_path != nullptr && *cache_path) cache_store(*P, cache_path, P->tile, win_ms);
+  // (the planner's own choice needs no record)
+  if (have && win.bl > 0 && cache_path != nullptr && *cache_path) cache_store(*P, cache_path, P->tile, win_ms);
   return have ? SPINSUM_OK : SPINSUM_ERR_UNSUPPORTED;
 }

@@ -703,3 +703,30 @@ def test_lds_pipeline_variant_needs_two_buffers():
     r = plan((2, 12, 12, 12), [[((0, 1, 2), 1.0)]])
     ss.spinsum_plan_set_tile(r, 3, variant=V)  # 24-byte rows
     assert ss.spinsum_plan_get_info(r)["variant"] == ss.SPINSUM_VARIANT_REG_ONESHOT
+
+
+@pytest.mark.parametrize("shape,gf,d,dtype,rows_bl", [
+    ((3, 33, 33, 33), 1, 3, "f64", 8), ((2, 35, 35, 35), 1, 3, "f64", 8),
+    ((2, 33, 33, 33), 1, 3, "f32", 8), ((2, 34, 34, 34), 1, 3, "f32", 8),
+    ((2, 35, 35, 35), 1, 3, "f32", 8), ((2, 27, 27, 27, 3), 1, 3, "f64", 6),
+    ((2, 11, 11, 11, 11), 1, 4, "f64", 4), ((1, 13, 13, 13, 13), 1, 4, "f64", 4),
+    ((1, 14, 14, 14, 14), 1, 4, "f32", 4), ((1, 151, 151), 1, 2, "f64", 40),
+    # the register tiles stay: 21^4 FP64, an explicit request, 16-byte rows
+    ((1, 21, 21, 21, 21), 1, 4, "f64", 0), ((2, 34, 34, 34), 1, 3, "f64", 0),
+    ((2, 25, 25, 25), 1, 3, "f64", 0),
+])
+def test_rows_tiling_rule(shape, gf, d, dtype, rows_bl):
+    """Where the planner's tile has no rows of whole 16-byte chunks, exec runs
+    on tiles of their own whose rows start on any element; the checker
+    replays both tilings."""
+    terms = [[(p, 1.0) for p in itertools.permutations(range(d))]]
+    p = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype, flags=HOST)
+    assert ss.spinsum_plan_get_info(p)["rows_bl"] == rows_bl
+    ok, why = ss.spinsum_plan_check_ownership(p)
+    assert ok, why
+    if rows_bl:
+        q = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype,
+                            flags=HOST | ss.SPINSUM_FLAG_NO_DIRECT_LDS)
+        assert ss.spinsum_plan_get_info(q)["rows_bl"] == 0
+        ss.spinsum_plan_set_tile(p, 3, variant=ss.SPINSUM_VARIANT_REG_ONESHOT)
+        assert ss.spinsum_plan_get_info(p)["rows_bl"] == 0
