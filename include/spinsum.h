@@ -193,6 +193,10 @@ typedef struct {
                             tiles of this edge with 16-byte loads and stores at any element
                             alignment; 0 where they run on the tile above (also after
                             spinsum_plan_set_tile with a tile edge) */
+  int unpack_gather;     /* spinsum_unpack forms every element where it is stored, from the
+                            packed values of its cube in LDS (the unpack_ fields above then
+                            describe the tiles it would otherwise run on): 1: one item per
+                            workgroup, 2: persistent; 0: on tiles */
 } spinsum_plan_info_t;
 
 /* Create a plan for Out = S_K(...S_1(In)) (Def. 3-4; in-place: Sec. 4.6.5).

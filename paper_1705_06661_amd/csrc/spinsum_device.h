@@ -237,6 +237,36 @@ struct PackArgs {
   int32_t tmpl_wg[kUnpackTemplates + 1];  // k_unpack_persist: first workgroup of each
 };
 
+// k_unpack_gather: one item is `cpi` whole cubes (persistent), or 1 / parts
+// of one cube.
+template <typename T>
+struct GatherArgs {
+  const T* packed;
+  T* full;
+  const T* coef;           // the operator's d! coefficients (forward vector)
+  int64_t cube_elems;      // of the full tensor
+  int64_t ncubes;
+  int64_t nitems;
+  int64_t xcd_per;
+  int32_t n;
+  int32_t inner;
+  int32_t ncomb;           // C(n, d)
+  int32_t rows;            // rows of one cube, n^(d-1)
+  int32_t cpi;             // cubes per item (1 where parts > 1)
+  int32_t parts;           // items per cube
+  int32_t part_rows;       // rows per part
+  int32_t batch;           // rows whose descriptions are in LDS at a time
+  int32_t buf_bytes;       // one buffer of packed values
+  int32_t row_off;         // LDS offset (bytes) of the coefficients and row descriptions
+  FastDiv fd_n;
+  FastDiv fd_rows;
+  FastDiv fd_cpr;          // / (n * inner / VW), columns of a row
+  FastDiv fd_inner;
+  int32_t sparse;          // the operator has a zero coefficient
+  int32_t rstep;           // rows stored at a time by the workgroup
+  int8_t slot[kMaxDF];     // coefficient of (order pattern of the row, position of k)
+};
+
 // Fused multiply-add in the storage type (a float FMA for float: the
 // generic builtin would promote to double).
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -2359,6 +2389,284 @@ __global__ void __launch_bounds__(kMaxThreads) k_unpack_persist(const PackArgs<T
   }
 }
 
+// Unpacking by gather: an item's packed values (those of whole cubes) are
+// copied into LDS as one contiguous run, and every element of the cubes is
+// formed where it is stored, in memory order: full[y] = a(tau^-1) v with v
+// the packed value of y's sorted tuple.  The elements of a group row
+// (i_0..i_{d-2}, all k) share the sorted order of the row's indices s: k at
+// position p among them gives the rank R_p - C(n-1-k, d-p), with
+//   R_p = C(n,d) - 1 - sum_{m<p} C(n-1-s_m, d-m) - sum_{m>=p} C(n-1-s_m, d-1-m)
+// (see increasing_rank).  The R_p of a batch of rows are worked out first,
+// one row per thread; then each thread keeps one column of the rows, so that
+// its k and their binomials stay in registers, and an element takes d - 1
+// comparisons and two LDS reads.  Bound by the stores: whole lines, and
+// nothing but the packed values is read (k_unpack scatters the values to
+// tiles in LDS first, which hold up to d! times as much).  Elements with
+// equal indices read a zero behind the packed values with a zero coefficient.
+// LDS: [packed values, 0 (row_off) | d! coefficients, 0 | row descriptions].
+
+// C(y, k) in 32 bits (y < 1024 for k <= 3, y < 256 for k = 4).
+__device__ __forceinline__ int small_binom(int y, int k) {
+  const uint32_t u = (uint32_t)y;
+  if (k == 1) return y;
+  const uint32_t c2 = u * (u - 1) / 2;
+  if (k == 2) return (int)c2;
+  const uint32_t c3 = u < 3 ? 0u : c2 * (u - 2) / 3;
+  return (int)(k == 3 ? c3 : u < 4 ? 0u : c3 * (u - 3) / 4);
+}
+
+// R: offset of the row's packed values in their buffer by the position of k
+// (the binomials of k to be taken off), in LDS bytes, for d = 4 in packed
+// entries, 16 bits each; meta: the sorted indices (10 bits each, d = 4: 8),
+// the order pattern of the row's indices (3 bits from bit 26), bit 31 where
+// two of them are equal.
+template <int D>
+struct alignas(16) RowDesc {
+  uint32_t w[4];
+};
+
+// step: LDS bytes per packed entry (inner elements); base: the first packed
+// entry of the row's cube
+template <int D>
+__device__ __forceinline__ RowDesc<D> describe_row(const int (&i)[D - 1], int n, int ncomb,
+                                                   int base, int step) {
+  int s[D - 1];
+  int pat = 0;
+  bool zero = false;
+  if constexpr (D == 2) {
+    s[0] = i[0];
+  } else if constexpr (D == 3) {
+    s[0] = min(i[0], i[1]);
+    s[1] = max(i[0], i[1]);
+    pat = i[0] > i[1] ? 1 : 0;
+    zero = i[0] == i[1];
+  } else {
+    const int lo = min(i[0], i[1]), hi = max(i[0], i[1]);
+    s[0] = min(lo, i[2]);
+    s[1] = max(lo, min(hi, i[2]));
+    s[2] = max(hi, i[2]);
+    pat = 2 * ((i[0] > i[1] ? 1 : 0) + (i[0] > i[2] ? 1 : 0)) + (i[1] > i[2] ? 1 : 0);
+    zero = s[0] == s[1] || s[1] == s[2];
+  }
+  int R[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int p = 0; p < D; ++p) {
+    int r = base + ncomb - 1;
+#pragma unroll
+    for (int m = 0; m < D - 1; ++m) r -= small_binom(n - 1 - s[m], m < p ? D - m : D - 1 - m);
+    R[p] = r;  // (no entry where no k stands at p)
+  }
+  uint32_t meta = ((uint32_t)pat << 26) | (zero ? 0x80000000u : 0u);
+#pragma unroll
+  for (int m = 0; m < D - 1; ++m) meta |= (uint32_t)s[m] << ((D == 4 ? 8 : 10) * m);
+  RowDesc<D> q;
+  if constexpr (D == 4) {
+    q.w[0] = ((uint32_t)R[0] & 0xFFFFu) | ((uint32_t)R[1] << 16);
+    q.w[1] = ((uint32_t)R[2] & 0xFFFFu) | ((uint32_t)R[3] << 16);
+    q.w[2] = 0;
+  } else {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) q.w[p] = (uint32_t)(R[p] * step);
+  }
+  q.w[3] = meta;
+  return q;
+}
+
+// LDS byte addresses of the packed value and of the coefficient of the
+// element at last index k of a described row (zero_v, zero_c: those of the
+// two zeros); g[m]: C(n-1-k, m + 1) packed entries, less the element's place
+// in the inner run, in the units of R.
+template <typename T, int D>
+__device__ __forceinline__ void gather_addr(const RowDesc<D>& q, int k, const int (&g)[D], int buf,
+                                            int step, int inner_off, int ctab, int zero_v, int zero_c,
+                                            int* va, int* ca) {
+  constexpr int kBits = D == 4 ? 8 : 10;
+  int R[4];
+  if constexpr (D == 4) {
+    R[0] = (int)(q.w[0] & 0xFFFFu);
+    R[1] = (int)(q.w[0] >> 16);
+    R[2] = (int)(q.w[1] & 0xFFFFu);
+    R[3] = (int)(q.w[1] >> 16);
+  } else {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) R[p] = (int)q.w[p];
+  }
+  const uint32_t meta = q.w[3];
+  bool ok = (int32_t)meta >= 0;
+  int c = ctab + (D == 2 ? 0 : (int)((meta >> 26) & 7u) * (D * (int)sizeof(T)));
+  int r = R[0] - g[D - 1];
+#pragma unroll
+  for (int m = 0; m < D - 1; ++m) {
+    const int sm = (int)((meta >> (kBits * m)) & ((1u << kBits) - 1u));
+    const int next = R[m + 1] - g[D - 2 - m];
+    r = k > sm ? next : r;
+    c += k > sm ? (int)sizeof(T) : 0;
+    ok = ok && k != sm;
+  }
+  const int off = D == 4 ? buf + r * step + inner_off : buf + r;
+  *va = ok ? off : zero_v;
+  *ca = ok ? c : zero_c;
+}
+
+// Issue the loads of m packed values into LDS, 16 bytes a lane at any
+// alignment of src; the last chunk may read up to VW - 1 values past them
+// where that many follow in the tensor (`follow`), else the last fewer than
+// VW values go through registers.
+template <typename T>
+__device__ __forceinline__ void packed_issue(const T* src, uint32_t m, bool follow, unsigned char* lds) {
+  constexpr uint32_t VW = 16 / sizeof(T);
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wave_bytes = (tid >> 6) * 1024u;
+  const uint32_t nch = follow ? (m + VW - 1) / VW : m / VW;
+  for (uint32_t c = 0; c < nch; c += blockDim.x)
+    if (c + tid < nch)
+      load_lds16<false>((const void*)(src + (size_t)(c + tid) * VW),
+                        (__attribute__((address_space(3))) void*)(lds + c * 16u + wave_bytes));
+  if (!follow && tid < m % VW)
+    reinterpret_cast<T*>(lds)[m / VW * VW + tid] = src[m / VW * VW + tid];
+}
+
+// PERSIST: the descriptions of an item's rows (the same for every item) are
+// made once, and while an item is stored the packed values of the next one
+// go to a second buffer; a workgroup of 1024 threads per CU walks its XCD's
+// range of items.  Fewer and longer streams of stores than with one item per
+// workgroup (32^3 FP64, 1 GB: 6.6 against 4.8 TB/s with three workgroups of
+// 512 threads a CU).  Otherwise (large cubes, or few) one item per workgroup,
+// `batch` rows described at a time.  Measured against the kernels on tiles,
+// 4.3 GB written: 32^3 FP64 925 against 1250 us, 48^3 925 against 1671, 8^3
+// 842 against 1474, 12^4 781 against 1388, 16^4 790 against 2196, 24^4 892
+// against 1855, 32^3 FP32 (2.1 GB) 497 against 541; non-temporal and cached
+// stores are the same.
+template <typename T, int D, bool PERSIST>
+__global__ void __launch_bounds__(kMaxThreads) k_unpack_gather(const GatherArgs<T> a) {
+  constexpr int DF = Fact<D>::v;
+  constexpr int VW = 16 / sizeof(T);
+  constexpr int B = VW == 2 ? 4 : 2;  // rows of a thread in flight
+  typedef typename VecT<T, VW>::type V;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int64_t x = blockIdx.x & 7u;
+  const int64_t nj = gridDim.x >> 3;
+  const int64_t end = min((x + 1) * a.xcd_per, a.nitems);
+  int64_t item = x * a.xcd_per + (int64_t)(blockIdx.x >> 3);
+  if (item >= end) return;
+  const int tid = (int)threadIdx.x;
+  const int n = a.n;
+  const int step = a.inner * (int)sizeof(T);
+  const int ctab = a.row_off;
+  const int zero_c = ctab + DF * (int)sizeof(T);
+  const int zero_v = zero_c;
+  if (tid < DF) reinterpret_cast<T*>(smem + ctab)[tid] = a.coef[a.slot[tid]];
+  if (tid == DF) *reinterpret_cast<T*>(smem + zero_c) = T(0);
+  RowDesc<D>* desc = reinterpret_cast<RowDesc<D>*>(smem + a.row_off + ((DF + 1) * sizeof(T) + 15) / 16 * 16);
+  // this thread's column of the rows
+  const int cpr = n * a.inner / VW;
+  const int row0 = (int)fdiv((uint32_t)tid, a.fd_cpr);
+  const int col = tid - row0 * cpr;
+  const int rstep = a.rstep;
+  int k[VW], g[VW][D], inner_off[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    const int y = col * VW + e;
+    k[e] = (int)fdiv((uint32_t)y, a.fd_inner);
+    inner_off[e] = (y - k[e] * a.inner) * (int)sizeof(T);
+#pragma unroll
+    for (int m = 0; m < D; ++m) {
+      const int bn = small_binom(n - 1 - k[e], m + 1);
+      g[e][m] = D == 4 ? bn : bn * step - inner_off[e];
+    }
+  }
+  // descriptions of rows [rb, rb + nrow) of an item
+  auto describe = [&](int rb, int nrow) {
+    for (int rr = tid; rr < nrow; rr += (int)blockDim.x) {
+      const uint32_t row = (uint32_t)(rb + rr);
+      const uint32_t ci = fdiv(row, a.fd_rows);
+      uint32_t rem = row - ci * (uint32_t)a.rows;
+      int i[D - 1];
+#pragma unroll
+      for (int m = D - 2; m >= 0; --m) {
+        const uint32_t qq = fdiv(rem, a.fd_n);
+        i[m] = (int)(rem - qq * (uint32_t)n);
+        rem = qq;
+      }
+      desc[rr] = describe_row<D>(i, n, a.ncomb, (int)ci * a.ncomb, step);
+    }
+  };
+  // the described rows from LDS buffer `buf`, stored from `out` on
+  auto store_rows = [&](int nrow, int buf, T* out) {
+    out += col * VW;
+    for (int r = row0; r < nrow; r += B * rstep) {
+      V val[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const RowDesc<D> q = desc[min(r + b * rstep, nrow - 1)];
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          int va, ca;
+          gather_addr<T, D>(q, k[e], g[e], buf, step, inner_off[e], ctab, zero_v, zero_c, &va, &ca);
+          const T v = *reinterpret_cast<const T*>(smem + va);
+          const T c = *reinterpret_cast<const T*>(smem + ca);
+          T w = c * v;
+          // a zero coefficient is not a term: 0 even for a non-finite v
+          if (a.sparse) w = c != T(0) ? w : T(0);
+          vset<V, T, VW>(val[b], e, w);
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (r + b * rstep < nrow)
+          __builtin_nontemporal_store(
+              val[b], reinterpret_cast<V*>(out + (int64_t)(r + b * rstep) * (cpr * VW)));
+    }
+  };
+  const int64_t ppc = (int64_t)a.ncomb * a.inner;  // packed values per cube
+  if constexpr (PERSIST) {
+    auto cubes_of = [&](int64_t it) { return (int)min((int64_t)a.cpi, a.ncubes - it * a.cpi); };
+    auto issue = [&](int64_t it, int buf) {
+      const int64_t c0 = it * a.cpi;
+      const int nc = cubes_of(it);
+      packed_issue<T>(a.packed + c0 * ppc, (uint32_t)(nc * ppc), (a.ncubes - c0 - nc) * ppc >= VW - 1,
+                      smem + buf);
+    };
+    issue(item, 0);
+    describe(0, a.cpi * a.rows);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the packed values are in LDS
+    lds_barrier();
+    // stores that every wave with a row issues per item, at least
+    const bool any_row = __builtin_amdgcn_ballot_w64(row0 < rstep) != 0ull;
+    int buf = 0;
+    for (;;) {
+      const int64_t next = item + nj;
+      const int other = a.buf_bytes - buf;
+      if (next < end) issue(next, other);
+      const int nrow = cubes_of(item) * a.rows;
+      if (row0 < rstep)
+        store_rows(nrow, buf, a.full + item * a.cpi * a.cube_elems);
+      if (next >= end) break;
+      // the next values are in LDS (this item's stores stay in flight), and
+      // every wave is done with this buffer
+      wait_vmcnt_atmost(any_row ? min(__builtin_amdgcn_readfirstlane(nrow / rstep), 31) : 0);
+      lds_barrier();
+      item = next;
+      buf = other;
+    }
+  } else {
+    const int64_t cube = (int64_t)((uint32_t)item / (uint32_t)a.parts);
+    const int part = (int)(item - cube * a.parts);
+    const int r_begin = part * a.part_rows;
+    const int r_end = min(r_begin + a.part_rows, a.rows);
+    packed_issue<T>(a.packed + cube * ppc, (uint32_t)ppc, (a.ncubes - cube - 1) * ppc >= VW - 1, smem);
+    for (int rb = r_begin; rb < r_end; rb += a.batch) {
+      const int nrow = min(a.batch, r_end - rb);
+      describe(rb, nrow);
+      if (rb == r_begin) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the values are in LDS
+      lds_barrier();  // (LDS only: the stores of the last batch stay in flight)
+      if (row0 < rstep)
+        store_rows(nrow, 0, a.full + cube * a.cube_elems + (int64_t)rb * (cpr * VW));
+      lds_barrier();  // the descriptions are rewritten
+    }
+  }
+}
+
 // Packing, the adjoint of unpacking: packed = E^T S^T full -- for every
 // strictly increasing x, sum_sigma a(sigma^-1) full[sigma . x].  The item's
 // tiles are loaded as in k_lds; nothing is stored to the full tensor.
@@ -2510,6 +2818,11 @@ const void* pack_kernel(bool pack, bool nts, bool persist) {
   return nts ? (const void*)k_unpack<T, D, true> : (const void*)k_unpack<T, D, false>;
 }
 
+template <typename T, int D>
+const void* gather_kernel(bool persist) {
+  return persist ? (const void*)k_unpack_gather<T, D, true> : (const void*)k_unpack_gather<T, D, false>;
+}
+
 template <typename T, int D, bool PERSIST>
 const void* batched_kernel_p(int vw) {
   if constexpr (sizeof(T) == 8) {
@@ -2535,7 +2848,8 @@ const void* batched_kernel(int vw, bool persist) {
   const void* pick_##tag##_d##d(int kind, int vw, bool chain, bool nts, int maxc);     \
   const void* pick_batched_##tag##_d##d(int vw, bool persist);                         \
   const void* pick_cgrad_##tag##_d##d(bool split);                                      \
-  const void* pick_pack_##tag##_d##d(bool pack, bool nts, bool persist);
+  const void* pick_pack_##tag##_d##d(bool pack, bool nts, bool persist);               \
+  const void* pick_gather_##tag##_d##d(bool persist);
 SPINSUM_DECLARE_PICK(f64, 2)
 SPINSUM_DECLARE_PICK(f64, 3)
 SPINSUM_DECLARE_PICK(f64, 4)

@@ -60,6 +60,19 @@ const void* pick_pack(int d, bool pack, bool nts, bool persist) {
 }
 
 template <typename T>
+const void* pick_gather(int d, bool persist) {
+  if constexpr (sizeof(T) == 8) {
+    if (d == 2) return pick_gather_f64_d2(persist);
+    if (d == 3) return pick_gather_f64_d3(persist);
+    return pick_gather_f64_d4(persist);
+  } else {
+    if (d == 2) return pick_gather_f32_d2(persist);
+    if (d == 3) return pick_gather_f32_d3(persist);
+    return pick_gather_f32_d4(persist);
+  }
+}
+
+template <typename T>
 const void* pick_cgrad(int d, bool split) {
   if constexpr (sizeof(T) == 8) {
     if (d == 2) return pick_cgrad_f64_d2(split);
@@ -698,6 +711,70 @@ spinsum_status launch_pack(spinsum_plan_s* P, const void* full, void* packed, bo
   return SPINSUM_OK;
 }
 
+// Unpacking by gather (k_unpack_gather).
+template <typename T>
+spinsum_status launch_gather(spinsum_plan_s* P, const void* packed, const void* full,
+                             hipStream_t stream) {
+  GatherArgs<T> a;
+  std::memset(&a, 0, sizeof(a));
+  const int64_t nc = ncomb_of(P->n, P->d);
+  a.packed = reinterpret_cast<const T*>(packed);
+  a.full = reinterpret_cast<T*>(const_cast<void*>(full));
+  a.coef = reinterpret_cast<const T*>(P->d_mats);  // the pre-multiplied forward vector
+  a.n = P->n;
+  a.inner = P->inner;
+  a.ncomb = (int32_t)nc;
+  a.rows = 1;
+  for (int m = 0; m + 1 < P->d; ++m) a.rows *= P->n;
+  a.cube_elems = (int64_t)a.rows * P->n * P->inner;
+  a.ncubes = P->ncubes;
+  a.cpi = P->pg_cpi;
+  a.parts = P->pg_parts;
+  a.part_rows = (a.rows + a.parts - 1) / a.parts;
+  a.batch = P->pg_batch;
+  a.nitems = (P->ncubes + a.cpi - 1) / a.cpi * a.parts;
+  const bool persist = P->pg_persist;
+  a.buf_bytes = (int32_t)gather_buf_bytes(*P, a.cpi, nc);
+  a.row_off = (persist ? 2 : 1) * a.buf_bytes;
+  constexpr int vw = 16 / (int)sizeof(T);
+  a.sparse = P->sparse_expanded != 0 ? 1 : 0;
+  // the rows that the threads store at a time end on a 128-byte line where
+  // that leaves at least one: a wave's stores are then whole lines (28^3
+  // FP32: 4.65 TB/s with 146 rows at a time, 5.59 with 144)
+  const int cpr = P->n * P->inner / vw;
+  int line = 8;
+  while (line > 1 && (cpr * (line / 2)) % 8 == 0) line /= 2;
+  a.rstep = P->pg_threads / cpr;
+  if (a.rstep > line) a.rstep = a.rstep / line * line;
+  a.fd_n = make_fastdiv((uint32_t)P->n);
+  a.fd_rows = make_fastdiv((uint32_t)a.rows);
+  a.fd_cpr = make_fastdiv((uint32_t)(P->n * P->inner / vw));
+  a.fd_inner = make_fastdiv((uint32_t)P->inner);
+  // slot[pattern * d + p]: the rank of tau^-1 for the element order tau with
+  // the last index at position p among the row's indices, which are ordered
+  // as the pattern-th permutation of d - 1
+  const int d = P->d;
+  for (int t = 0; t < P->G.df; ++t) {
+    const std::vector<int>& tau = P->G.p[t];
+    const int p = tau[d - 1];
+    int q[kMaxD] = {0, 0, 0, 0};
+    for (int m = 0; m + 1 < d; ++m) q[m] = tau[m] - (tau[m] > p ? 1 : 0);
+    a.slot[lex_rank(d - 1, q) * d + p] = (int8_t)P->G.inv[t];
+  }
+  const void* k = pick_gather<T>(d, persist);
+  const size_t shmem = (size_t)gather_lds_bytes(*P, a.cpi, nc, a.batch, persist);
+  spinsum_status st = prepare_kernel(P, k, shmem);
+  if (st != SPINSUM_OK) return st;
+  a.xcd_per = (a.nitems + 7) / 8;
+  // persistent: one workgroup per CU, one share per XCD
+  const int64_t resident = std::max<int64_t>(1, P->num_cus / 8);
+  const int64_t per_xcd = persist ? std::min<int64_t>(a.xcd_per, resident) : a.xcd_per;
+  void* kargs[] = {&a};
+  hipError_t e = hipLaunchKernel(k, dim3((unsigned)(per_xcd * 8)), dim3(P->pg_threads), kargs, shmem, stream);
+  if (e != hipSuccess) return hip_error(P, e);
+  return SPINSUM_OK;
+}
+
 spinsum_status pack_impl(spinsum_plan_s* P, const void* full, void* packed, bool pack,
                          void* stream) {
   if (P == nullptr || P->batched) return SPINSUM_ERR_INVALID_ARG;
@@ -721,6 +798,10 @@ spinsum_status pack_impl(spinsum_plan_s* P, const void* full, void* packed, bool
   const bool whole = Tl.g.bl == Tl.g.n;
   const bool rows = Tl.vw * esz == 16;
   if (P->tile.lds_pad != 0 || !(whole || rows)) return SPINSUM_ERR_UNSUPPORTED;
+  if (!pack && P->pk_gather && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) {
+    if (P->dtype == SPINSUM_F32) return launch_gather<float>(P, packed, full, (hipStream_t)stream);
+    return launch_gather<double>(P, packed, full, (hipStream_t)stream);
+  }
   if (P->dtype == SPINSUM_F32) return launch_pack<float>(P, full, packed, pack, (hipStream_t)stream);
   return launch_pack<double>(P, full, packed, pack, (hipStream_t)stream);
 }

@@ -16,4 +16,6 @@ const void* pick_pack_f32_d2(bool pack, bool nts, bool persist) {
   return pack_kernel<float, 2>(pack, nts, persist);
 }
 
+const void* pick_gather_f32_d2(bool persist) { return gather_kernel<float, 2>(persist); }
+
 }  // namespace spinsum

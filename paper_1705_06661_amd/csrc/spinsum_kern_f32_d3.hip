@@ -16,4 +16,6 @@ const void* pick_pack_f32_d3(bool pack, bool nts, bool persist) {
   return pack_kernel<float, 3>(pack, nts, persist);
 }
 
+const void* pick_gather_f32_d3(bool persist) { return gather_kernel<float, 3>(persist); }
+
 }  // namespace spinsum

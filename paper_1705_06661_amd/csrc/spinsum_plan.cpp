@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <cstdlib>
 #include <map>
 #include <numeric>
 #include <utility>
@@ -795,6 +796,74 @@ static void choose_unpack_tiling(spinsum_plan_s* P) {
   }
 }
 
+// LDS of k_unpack_gather: one or two buffers of the packed values of cpi
+// cubes, the coefficients with a zero, 16 bytes per described row.
+int64_t gather_buf_bytes(const spinsum_plan_s& P, int64_t cpi, int64_t ncomb) {
+  return (cpi * ncomb * P.inner * elem_size(P) + 15) / 16 * 16;
+}
+int64_t gather_lds_bytes(const spinsum_plan_s& P, int64_t cpi, int64_t ncomb, int64_t rows,
+                         bool persist) {
+  return (persist ? 2 : 1) * gather_buf_bytes(P, cpi, ncomb) +
+         ((P.G.df + 1) * elem_size(P) + 15) / 16 * 16 + rows * 16;
+}
+
+// Unpacking by gather where rows are whole 16-byte chunks and the packed
+// values of a cube fit a CU's LDS: it reads nothing but those and stores
+// whole lines, at up to 2.8 times the rate of the kernels on tiles (figures
+// at k_unpack_gather).  The kernels on tiles stay for
+//  - whole cubes run persistently (choose_unpack_tiling) of 80 KiB and more,
+//    FP32 48 KiB (its gather takes twice the instructions per byte), or with
+//    inner runs, which scatter long runs: 24^3 FP64 5.76 against 5.2 TB/s,
+//    28^3 FP32 6.39 against 4.9, 16^3 x 3 6.80 against 6.15; not for edges
+//    of whole LDS rows (32^3 FP32 4.57 against 5.0);
+//  - too few cubes to fill the CUs (ten 48^3 cubes: 7.7 against 13.2 us), or
+//    small ones of less than 64 MiB in all (600 16^3 cubes: 9.9 against 11.1).
+static void choose_unpack_gather(spinsum_plan_s* P) {
+  P->pk_gather = false;
+  if (P->pair || P->batched || P->ncubes <= 0 || P->elems <= 0) return;
+  const int d = P->d, n = P->n, esz = elem_size(*P);
+  if (n < d || n > (d == 4 ? 255 : 1023)) return;
+  int64_t nc = 1;
+  for (int k = 0; k < d; ++k) nc = nc * (n - k) / (k + 1);
+  const int64_t rows = ipow(n, d - 1);
+  const int64_t row = (int64_t)n * P->inner;
+  const int64_t cube_bytes = rows * row * esz;
+  const int64_t cus = P->num_cus;
+  if (row * esz % 16 != 0 || row * esz / 16 > 1024) return;
+  if (d == 3 && P->pk_own && P->pk_persist && P->Tu.g.bl == n &&
+      (P->inner > 1 || (cube_bytes >= (esz == 4 ? 48 : 80) * 1024 && n % 32 != 0)))
+    return;
+  if (cube_bytes <= 32 * 1024 && P->elems * esz < (64 << 20)) return;
+  P->pg_parts = 1;
+  P->pg_threads = 1024;
+  // persistent: items of at least 128 KiB, while that leaves two for every
+  // workgroup
+  int64_t cpi = std::max<int64_t>(1, (128 * 1024 + cube_bytes - 1) / cube_bytes);
+  cpi = std::min(cpi, std::max<int64_t>(1, P->ncubes / (2 * cus)));
+  auto lds_of = [&](int64_t c) { return gather_lds_bytes(*P, c, nc, c * rows, true); };
+  while (cpi > 1 && lds_of(cpi) > P->lds_limit) --cpi;
+  P->pg_persist = lds_of(cpi) <= P->lds_limit && (d < 4 || nc * cpi < 65536) && P->ncubes >= 2 * cus;
+  if (P->pg_persist) {
+    P->pg_cpi = (int)cpi;
+    P->pg_batch = (int)(cpi * rows);
+  } else {
+    // one item per workgroup: with few cubes several items per cube, each
+    // with all packed values in LDS, down to twice their bytes stored
+    P->pg_cpi = 1;
+    P->pg_batch = 512;
+    const int64_t lds = gather_lds_bytes(*P, 1, nc, P->pg_batch, false);
+    if (lds > P->lds_limit || (d == 4 && nc > 65535)) return;
+    const int64_t want = (4 * cus + P->ncubes - 1) / P->ncubes;
+    P->pg_parts = (int)std::max<int64_t>(1, std::min<int64_t>({want, (int64_t)P->G.df / 2, rows}));
+    if (P->ncubes * P->pg_parts < cus) return;
+    const int64_t per_cu = P->lds_limit / lds;
+    P->pg_threads = per_cu >= 4 ? 256 : per_cu >= 2 ? 512 : 1024;
+    if (row * esz / 16 > P->pg_threads) P->pg_threads = 1024;
+  }
+  if ((P->ncubes + P->pg_cpi - 1) / P->pg_cpi * P->pg_parts >= (1ll << 31) - 8) return;
+  P->pk_gather = true;
+}
+
 // The sum's tiles for k_rows where the planner's default is the register
 // path (no edge has rows of whole 16-byte chunks: odd extents above all).
 // k_rows loads and stores 16 bytes a lane at any element alignment, so the
@@ -858,6 +927,7 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
   free_device(P);
   P->cg_split = cgrad_split_ok(*P);
   choose_unpack_tiling(P);
+  choose_unpack_gather(P);
   if (P->flags & SPINSUM_FLAG_HOST_ONLY) return SPINSUM_OK;
   spinsum_status st;
   // coefficient vectors in the storage type: forward | adjoint | stages | adjoint stages
@@ -1748,6 +1818,8 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
     info->unpack_persistent =
         (P->pk_own && P->pk_persist && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 1 : 0;
     info->unpack_nt_stores = (P->pk_own ? P->Tu.nts : P->T.nts) != 0 ? 1 : 0;
+    info->unpack_gather =
+        (P->pk_gather && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? (P->pg_persist ? 2 : 1) : 0;
     return SPINSUM_OK;
   }
   std::memset(info, 0, sizeof(*info));
@@ -1781,6 +1853,8 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
       (!P->batched && !P->pair && (P->pk_own ? P->Tu.nts : P->T.nts) != 0) ? 1 : 0;
   info->unpack_persistent = (!P->batched && !P->pair && P->pk_own && P->pk_persist &&
                         !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 1 : 0;
+  info->unpack_gather =
+      (P->pk_gather && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? (P->pg_persist ? 2 : 1) : 0;
   info->rows_bl = P->x_rows ? P->Tx.g.bl : 0;
   info->batch_item_bytes = P->batched ? P->batch_item_bytes : 0;
   info->batch_persistent = P->batched ? P->batch_persistent : 0;

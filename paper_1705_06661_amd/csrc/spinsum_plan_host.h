@@ -114,6 +114,15 @@ struct spinsum_plan_s {
   bool pk_persist = false;
   int pk_persist_blocks = 1;
 
+  // unpacking by gather (k_unpack_gather, see choose_unpack_gather): cubes per
+  // item, items per cube, rows described at a time, workgroup size
+  bool pk_gather = false;
+  int pg_cpi = 1;
+  int pg_parts = 1;
+  int pg_batch = 256;
+  int pg_threads = 256;
+  bool pg_persist = false;
+
   // index-pair form (SPINSUM_FLAG_INDEX_PAIRS): T.g describes one pair
   // block, T.reps holds the representative pool, T.nb / T.vw / T.ragged /
   // T.max_tiles / T.max_rep_cnt / T.lds_elems / T.nitems as for tile orbits
@@ -179,6 +188,9 @@ spinsum_status upload_tables(spinsum_plan_s* P);
 spinsum_status build_batched(spinsum_plan_s* P, int64_t item_bytes);
 void free_device(spinsum_plan_s* P);
 int elem_size(const spinsum_plan_s& P);
+int64_t gather_buf_bytes(const spinsum_plan_s& P, int64_t cpi, int64_t ncomb);
+int64_t gather_lds_bytes(const spinsum_plan_s& P, int64_t cpi, int64_t ncomb, int64_t rows,
+                         bool persist);
 // Implemented in spinsum_exec.hip
 spinsum_status cache_occupancy(spinsum_plan_s* P);
 // Implemented in spinsum_tune.cpp
