@@ -188,11 +188,14 @@ typedef struct {
                             before the current item's stores; 0: one item per
                             workgroup */
   int unpack_nt_stores;  /* 1: unpacking stores with the non-temporal policy */
-  int rows_bl;           /* tile edge of exec and adjoint where the planner's tile (the fields
-                            above) has no rows of whole 16-byte chunks: they then run on
-                            tiles of this edge with 16-byte loads and stores at any element
-                            alignment; 0 where they run on the tile above (also after
-                            spinsum_plan_set_tile with a tile edge) */
+  int sum_bl;            /* tile edge of exec and adjoint where they run on tiles of their own
+                            instead of the planner's tile (the fields above): where its rows
+                            are not whole 16-byte chunks, tiles whose rows are loaded and
+                            stored in 16-byte pieces at any element alignment; where they
+                            are parts of 128-byte lines although a cube fits a CU's LDS (at
+                            least two cubes per CU, d <= 3), whole cubes.  0 where they run
+                            on the tile above (also after spinsum_plan_set_tile with a tile
+                            edge) */
   int unpack_gather;     /* spinsum_unpack forms every element where it is stored, from the
                             packed values of its cube in LDS (the unpack_ fields above then
                             describe the tiles it would otherwise run on): 1: one item per

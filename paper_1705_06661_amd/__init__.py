@@ -94,7 +94,7 @@ class _Info(ctypes.Structure):
                 ("persistent_per_cu", ctypes.c_int), ("nt_loads", ctypes.c_int),
                 ("coef_grad_split", ctypes.c_int), ("unpack_bl", ctypes.c_int),
                 ("unpack_persistent", ctypes.c_int), ("unpack_nt_stores", ctypes.c_int),
-                ("rows_bl", ctypes.c_int), ("unpack_gather", ctypes.c_int)]
+                ("sum_bl", ctypes.c_int), ("unpack_gather", ctypes.c_int)]
 
 
 _vp = ctypes.c_void_p

@@ -1331,6 +1331,110 @@ __global__ void __launch_bounds__(kMaxThreads) k_rows(const ExecArgs<T> a) {
   store_rows_lds<T, D, NTS>(g, od, ntl, a.out + cube0 * g.cube_elems, lds);
 }
 
+// Word 3 of a raw buffer resource on gfx9 (32-bit data format; a raw buffer
+// checks byte offsets against the size in word 2).
+constexpr int kBufferFlags = 0x00027000;
+
+// Whole cubes of which one fits a CU, persistent: a workgroup of 1024 threads
+// walks its XCD's range of cubes.  While a cube is combined in LDS the next
+// one is on its way into registers (U chunks of 16 bytes per thread, at any
+// alignment of the cube); each thread then stores its chunks of the combined
+// cube and puts the next cube's in their place, so both directions of memory
+// traffic run on under the combine step.  With one workgroup per cube the CU
+// has nothing in flight while it combines.  The representative list is in
+// LDS for good: a vector load in the combine step would wait for the
+// prefetch, since vector loads complete in order.
+// LDS: [cube (lds_tile_bytes) | representatives].
+template <typename T, int D, bool CHAIN, int U>
+__global__ void __launch_bounds__(kMaxThreads) k_cube(const ExecArgs<T> a) {
+  constexpr int VW = 16 / sizeof(T);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T* lds = reinterpret_cast<T*>(smem);
+  uint32_t* rep_lds = reinterpret_cast<uint32_t*>(smem + a.lds_tile_bytes);
+  const Geom& g = a.g;
+  const int64_t x = blockIdx.x & 7u;
+  const int64_t nj = gridDim.x >> 3;
+  int64_t end = (x + 1) * a.xcd_per;
+  if (end > a.nitems) end = a.nitems;
+  int64_t cube = x * a.xcd_per + (int64_t)(blockIdx.x >> 3);
+  if (cube >= end) return;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t m = (uint32_t)g.cube_elems;
+  const uint32_t nfull = m / VW, tail = m % VW;
+  const cptr<GroupDev> od = as_const(a.orbits);
+  const cptr<T> coef = as_const(a.coef);
+  // buffer instructions: chunks past the cube load nothing and store nothing
+  // without a branch, so that the compiler counts the operations in flight
+  // exactly and waits for no more than the chunk it needs
+  typedef uint32_t W __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  constexpr int kNt = 2;  // non-temporal policy
+  W buf[U];
+  T end_val;  // thread e < tail: the cube's element nfull * VW + e
+  auto load = [&](int64_t c) {
+    T* src = const_cast<T*>(a.in + c * g.cube_elems);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(src, 0, (int)(nfull * 16u), kBufferFlags);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      buf[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((tid + (uint32_t)u * kMaxThreads) * 16u), 0, kNt);
+    const __amdgpu_buffer_rsrc_t re =
+        __builtin_amdgcn_make_buffer_rsrc(src + nfull * VW, 0, (int)(tail * sizeof(T)), kBufferFlags);
+    if constexpr (sizeof(T) == 8)
+      end_val = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(re, (int)(tid * 8u), 0, 0));
+    else
+      end_val = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(re, (int)(tid * 4u), 0, 0));
+  };
+  auto fill = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t q = tid + (uint32_t)u * kMaxThreads;
+      if (q < nfull) *reinterpret_cast<W*>(lds + q * VW) = buf[u];
+    }
+    if (tid < tail) lds[nfull * VW + tid] = end_val;
+  };
+  load(cube);
+  {
+    const uint32_t cnt = (uint32_t)od->rep_cnt[0];
+    const uint32_t* rsrc = a.reps + od->rep_off[0];
+    for (uint32_t i = tid; i < cnt; i += kMaxThreads) rep_lds[i] = rsrc[i];
+  }
+  fill();
+  for (;;) {
+    clear_terms_flag(a.sparse);
+    const int64_t next = cube + nj;
+    if (next < end) load(next);
+    lds_barrier();
+    const bool bad = combine_item<T, D, CHAIN, true>(g, od, rep_lds, coef, a.nstages, 1, lds);
+    // the vote of item_needs_terms, with barriers that leave the prefetch in
+    // flight
+    if (a.sparse != 0u && __builtin_amdgcn_ballot_w64(bad) != 0ull && (tid & 63u) == 0u)
+      __hip_atomic_fetch_or(&terms_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    lds_barrier();
+    if (a.sparse != 0u && terms_flag != 0u) {
+      redo_item<T, D, CHAIN, true>(g, od, rep_lds, coef, a.nstages, 1, a.in + cube * g.cube_elems, lds);
+      lds_barrier();
+    }
+    T* dst = a.out + cube * g.cube_elems;
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(dst, 0, (int)(nfull * 16u), kBufferFlags);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t q = tid + (uint32_t)u * kMaxThreads;
+      const W val = *reinterpret_cast<const W*>(lds + min(q, nfull - 1) * VW);
+      __builtin_amdgcn_raw_buffer_store_b128(val, rd, (int)(q * 16u), 0, kNt);
+    }
+    const T last = lds[nfull * VW - 1 + min(tid + 1, tail)];
+    const __amdgpu_buffer_rsrc_t re =
+        __builtin_amdgcn_make_buffer_rsrc(dst + nfull * VW, 0, (int)(tail * sizeof(T)), kBufferFlags);
+    if constexpr (sizeof(T) == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, last), re, (int)(tid * 8u), 0, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, last), re, (int)(tid * 4u), 0, 0);
+    if (next >= end) break;
+    fill();  // (each thread its own chunks: no barrier between)
+    cube = next;
+  }
+}
+
 // Index-pair form: one tile orbit {sigma . c} of one pair block per
 // workgroup, c the orbit's sorted combined blocks (c_m = a_m * nb + b_m).
 // Every wave forms the tile list itself: lane r forms sigma_r . c; tiles are
@@ -2771,12 +2875,20 @@ const void* pipe_kernel(int vw) {
 
 // kind: 1 direct-LDS one-shot, 2 register-prefetch persistent (maxc = 8 or
 // 16), 3 register one-shot, 4 direct-LDS double-buffered persistent,
-// 5 index-pair form (direct-LDS one-shot), 6 tile rows of any alignment
+// 5 index-pair form (direct-LDS one-shot), 6 tile rows of any alignment,
+// 7 whole cubes with the next one in registers (maxc chunks per thread)
 template <typename T, int D>
 const void* pick_d(int kind, int vw, bool chain, bool nts, int maxc) {
   if (kind == 5) {
     if (chain) return nts ? (const void*)k_pair<T, D, true, true> : (const void*)k_pair<T, D, true, false>;
     return nts ? (const void*)k_pair<T, D, false, true> : (const void*)k_pair<T, D, false, false>;
+  }
+  if (kind == 7) {
+    if constexpr (D <= 3) {
+      if (maxc == 8) return chain ? (const void*)k_cube<T, D, true, 8> : (const void*)k_cube<T, D, false, 8>;
+      return chain ? (const void*)k_cube<T, D, true, 10> : (const void*)k_cube<T, D, false, 10>;
+    }
+    return nullptr;
   }
   if (kind == 6) {
     if (chain) return nts ? (const void*)k_rows<T, D, true, true> : (const void*)k_rows<T, D, true, false>;

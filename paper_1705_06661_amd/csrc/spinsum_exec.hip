@@ -112,15 +112,22 @@ struct LaunchCfg {
 template <typename T>
 LaunchCfg exec_cfg(const spinsum_plan_s* P, bool chain) {
   LaunchCfg c;
-  if (P->x_rows) {
-    const Tiling& Tx = P->Tx;
+  const Tiling& Tl = P->x_own ? P->Tx : P->T;
+  if (cube_persistent(*P, Tl)) {
+    const int64_t chunks = Tl.g.cube_elems * (int64_t)sizeof(T) / 16;
+    c.kind = kKindCube;
+    c.k = pick_kernel<T>(P->d, c.kind, Tl.vw, chain, true, chunks <= 8 * kMaxThreads ? 8 : 10);
+    c.shmem = ((size_t)Tl.lds_elems * sizeof(T) + 15) / 16 * 16 + (size_t)Tl.max_rep_cnt * 4;
+    c.threads = kMaxThreads;
+    return c;
+  }
+  if (P->x_own) {
     c.kind = kVariantAnyRows;
-    c.k = pick_kernel<T>(P->d, c.kind, Tx.vw, chain, Tx.nts != 0, 0);
-    c.shmem = ((size_t)Tx.lds_elems * sizeof(T) + 15) / 16 * 16 + (size_t)Tx.max_rep_cnt * 4;
+    c.k = pick_kernel<T>(P->d, c.kind, Tl.vw, chain, Tl.nts != 0, 0);
+    c.shmem = ((size_t)Tl.lds_elems * sizeof(T) + 15) / 16 * 16 + (size_t)Tl.max_rep_cnt * 4;
     c.threads = P->x_threads;
     return c;
   }
-  const Tiling& Tl = P->T;
   const bool nts = Tl.nts != 0;
   int kind = P->tile.variant;
   if (!nts && kind == SPINSUM_VARIANT_REG_PIPELINE) kind = SPINSUM_VARIANT_REG_ONESHOT;
@@ -202,15 +209,15 @@ CoefSel stage_sel(const spinsum_plan_s* P, bool adjoint, int j) {
 template <typename T>
 spinsum_status launch_exec(spinsum_plan_s* P, const void* in, void* out, hipStream_t stream,
                            const CoefSel& sel) {
-  const Tiling& Tl = P->x_rows ? P->Tx : P->T;
+  const Tiling& Tl = P->x_own ? P->Tx : P->T;
   if (Tl.nitems <= 0) return SPINSUM_OK;
   const T* coef = reinterpret_cast<const T*>(P->d_mats);
   ExecArgs<T> a;
   std::memset(&a, 0, sizeof(a));
   a.in = reinterpret_cast<const T*>(in);
   a.out = reinterpret_cast<T*>(out);
-  a.orbits = reinterpret_cast<const GroupDev*>(P->x_rows ? P->d_x_orbits : P->d_orbits);
-  a.reps = reinterpret_cast<const uint32_t*>(P->x_rows ? P->d_x_reps : P->d_reps);
+  a.orbits = reinterpret_cast<const GroupDev*>(P->x_own ? P->d_x_orbits : P->d_orbits);
+  a.reps = reinterpret_cast<const uint32_t*>(P->x_own ? P->d_x_reps : P->d_reps);
   a.coef = coef + sel.offset;
   a.nstages = sel.nstages;
   a.sparse = sel.sparse;
@@ -225,7 +232,10 @@ spinsum_status launch_exec(spinsum_plan_s* P, const void* in, void* out, hipStre
   spinsum_status st = prepare_kernel(P, c.k, c.shmem);
   if (st != SPINSUM_OK) return st;
   int64_t grid;
-  if (c.persistent) {
+  if (c.kind == kKindCube) {  // one persistent workgroup per CU
+    a.xcd_per = (Tl.nitems + 7) / 8;
+    grid = std::max<int64_t>(8, (int64_t)P->num_cus / 8 * 8);
+  } else if (c.persistent) {
     grid = persistent_grid(P, Tl.nitems);
     a.xcd_per = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) ? 0 : (Tl.nitems + 7) / 8;
   } else if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {

@@ -864,6 +864,47 @@ static void choose_unpack_gather(spinsum_plan_s* P) {
   P->pk_gather = true;
 }
 
+// Whole cubes of which one fits a CU, at least two per workgroup: k_cube.
+// (Two or more cubes to a CU hide each other's combine step already: 20^3
+// FP64 6.08 TB/s with k_lds, 5.94 with k_cube; 24^3 FP32 6.00 and 5.26.)
+bool cube_persistent(const spinsum_plan_s& P, const Tiling& T) {
+  if (P.pair || P.batched || P.d > 3 || P.n <= 0 || T.g.bl != P.n || T.g.cpw != 1 ||
+      P.tile.variant != SPINSUM_VARIANT_DIRECT_LDS || P.ncubes < 2 * (int64_t)P.num_cus)
+    return false;
+  if (!T.nts || !T.ntl || (P.flags & (SPINSUM_FLAG_NO_XCD_REMAP | SPINSUM_FLAG_REVERSE_ORDER)))
+    return false;
+  const int64_t lds = (T.lds_elems * elem_size(P) + 15) / 16 * 16 + (int64_t)T.max_rep_cnt * 4;
+  return P.lds_limit / lds < 2;
+}
+
+// The sum on whole cubes (k_cube) where the planner's default is tiles of
+// one orbit an item whose rows are parts of lines, and a cube fits a CU:
+// 24^3 FP64 in place 6.00 against 5.47 TB/s on 8^3 tiles, 120^2 FP64 5.93
+// against 5.53 on 40^2.  (Tiles of whole lines are as good: 12^3 with inner
+// runs of 8, 6.08 against 5.99; so are 16^3 FP32 tiles, two orbits an item,
+// on 32^3: 4.83 against 4.65.)
+static void choose_cube_tiling(spinsum_plan_s* P) {
+  const Tiling& T = P->T;
+  const int esz = elem_size(*P);
+  if (P->x_own || P->pair || P->batched || P->d > 3 || P->ncubes <= 0 || P->n <= 0 ||
+      T.g.bl >= P->n || P->tile.variant != SPINSUM_VARIANT_DIRECT_LDS || P->tile.item_tiles != 0 ||
+      ((int64_t)T.g.bl * P->inner * esz) % 128 == 0 ||
+      ipow(P->n, P->d) * P->inner * esz > P->lds_limit)
+    return;
+  spinsum_tile_t t{};
+  t.bl = P->n;
+  t.cubes_per_wg = 1;
+  t.variant = SPINSUM_VARIANT_DIRECT_LDS;
+  Tiling Tx;
+  const int vmax = max_vector_width(*P, (int64_t)P->n * P->inner);
+  if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tx) != SPINSUM_OK || !Tx.fits) return;
+  Tx.nts = choose_nts(*P, Tx, (int64_t)Tx.orbits.size());
+  Tx.ntl = choose_ntl(*P, Tx);
+  if (!cube_persistent(*P, Tx)) return;
+  P->Tx = std::move(Tx);
+  P->x_own = true;
+}
+
 // The sum's tiles for k_rows where the planner's default is the register
 // path (no edge has rows of whole 16-byte chunks: odd extents above all).
 // k_rows loads and stores 16 bytes a lane at any element alignment, so the
@@ -875,7 +916,7 @@ static void choose_unpack_gather(spinsum_plan_s* P) {
 // the L2 merges (37^3 FP32 out of place 3.10 against 1.51 TB/s
 // non-temporal; 33^3 FP64 3.77 against 3.65).
 static void choose_rows_tiling(spinsum_plan_s* P) {
-  P->x_rows = false;
+  P->x_own = false;
   if (P->pair || P->batched || P->ncubes <= 0 || P->elems <= 0 || P->n <= 0 ||
       P->T.g.bl >= P->n || P->tile.variant != SPINSUM_VARIANT_REG_ONESHOT ||
       (P->flags & SPINSUM_FLAG_NO_DIRECT_LDS) || (int64_t)P->T.vw * elem_size(*P) == 16)
@@ -918,7 +959,7 @@ static void choose_rows_tiling(spinsum_plan_s* P) {
       P->x_threads = per_cu >= 4 ? 256 : per_cu >= 2 ? 512 : 1024;
       Tx.nts = (P->flags & SPINSUM_FLAG_NT_STORES) ? 1 : 0;
       P->Tx = std::move(Tx);
-      P->x_rows = true;
+      P->x_own = true;
       return;
     }
 }
@@ -949,9 +990,9 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
     st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
     if (st != SPINSUM_OK) return st;
   } else if (!P->batched) {
-    // (with x_rows nothing runs on T: the coefficient gradient and packing
+    // (with k_rows nothing runs on T: the coefficient gradient and packing
     // refuse rows that are not whole 16-byte chunks)
-    if (!P->x_rows) {
+    if (!(P->x_own && P->Tx.any_rows)) {
       st = upload(P, &P->d_orbits, P->T.groups.data(), P->T.groups.size());
       if (st != SPINSUM_OK) return st;
       st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
@@ -961,7 +1002,7 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
         if (st != SPINSUM_OK) return st;
       }
     }
-    if (P->x_rows) {
+    if (P->x_own) {
       st = upload(P, &P->d_x_orbits, P->Tx.groups.data(), P->Tx.groups.size());
       if (st != SPINSUM_OK) return st;
       st = upload(P, &P->d_x_reps, P->Tx.reps.data(), P->Tx.reps.size());
@@ -1413,8 +1454,11 @@ static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req) {
   T.ntl = choose_ntl(*P, T);
   P->tile = t;
   P->T = std::move(T);
-  P->x_rows = false;
-  if (chosen) choose_rows_tiling(P);
+  P->x_own = false;
+  if (chosen) {
+    choose_rows_tiling(P);
+    choose_cube_tiling(P);
+  }
   return SPINSUM_OK;
 }
 
@@ -1783,7 +1827,7 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
   const PairGeom keep_pg = P->pg;
   const std::vector<uint64_t> keep_orbits = P->pair_orbits;
   const Tiling keep_tx = P->Tx;
-  const bool keep_rows = P->x_rows;
+  const bool keep_own = P->x_own;
   const int keep_x_threads = P->x_threads;
   spinsum_status st = apply_tile(P, tile);
   if (st == SPINSUM_OK) st = upload_tables(P);
@@ -1793,7 +1837,7 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
     P->pg = keep_pg;
     P->pair_orbits = keep_orbits;
     P->Tx = keep_tx;
-    P->x_rows = keep_rows;
+    P->x_own = keep_own;
     P->x_threads = keep_x_threads;
     spinsum_status st2 = upload_tables(P);
     (void)st2;
@@ -1855,7 +1899,7 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
                         !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 1 : 0;
   info->unpack_gather =
       (P->pk_gather && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? (P->pg_persist ? 2 : 1) : 0;
-  info->rows_bl = P->x_rows ? P->Tx.g.bl : 0;
+  info->sum_bl = P->x_own ? P->Tx.g.bl : 0;
   info->batch_item_bytes = P->batched ? P->batch_item_bytes : 0;
   info->batch_persistent = P->batched ? P->batch_persistent : 0;
   if (!P->batched) {
@@ -2254,7 +2298,7 @@ extern "C" spinsum_status spinsum_plan_check_ownership(spinsum_plan_t P, int blo
   }
   const std::string bad = check_tiling(*P, T0);
   if (!bad.empty()) return fail(bad);
-  if (P->x_rows) {  // the tiles the sum runs on
+  if (P->x_own) {  // the tiles the sum runs on
     const std::string bad_rows = check_tiling(*P, P->Tx);
     if (!bad_rows.empty()) return fail(bad_rows);
   }

@@ -98,11 +98,12 @@ struct spinsum_plan_s {
   // tile's chunks in one pass of the workgroup, no inner runs, d <= 3
   // (decided with the tables, upload_tables)
   bool cg_split = false;
-  // The sum's own tiling for k_rows (see choose_rows_tiling): where the plan's
-  // default tiles have no rows of whole 16-byte chunks, exec and adjoint run
-  // on these tiles instead of T's register tiles
+  // The sum's own tiling (x_own): where the plan's default tiles have no rows
+  // of whole 16-byte chunks, or part lines although a cube fits a CU, exec
+  // and adjoint run on these tiles instead of T (choose_rows_tiling, k_rows;
+  // choose_cube_tiling, k_cube)
   spinsum::Tiling Tx;
-  bool x_rows = false;
+  bool x_own = false;
   int x_threads = 256;
   // unpacking's own tiling where it differs from T (pk_own): the largest
   // items that fit a CU (see build_unpack_tiling), with their workgroup size
@@ -164,7 +165,7 @@ struct spinsum_plan_s {
   void* d_cg_reps = nullptr;
   void* d_pk_orbits = nullptr;  // Tu.groups, Tu.reps (pk_own)
   void* d_pk_reps = nullptr;
-  void* d_x_orbits = nullptr;  // Tx.groups, Tx.reps (x_rows)
+  void* d_x_orbits = nullptr;  // Tx.groups, Tx.reps (x_own)
   void* d_x_reps = nullptr;
   int last_hip_error = 0;
   int occ_blocks = 1;  // workgroups per CU of the persistent exec kernel (cache_occupancy)
@@ -175,6 +176,9 @@ namespace spinsum {
 // Tile variant of Tiling::any_rows (k_rows): chosen by the planner for Tx,
 // never requested.
 constexpr int kVariantAnyRows = 6;
+// Kernel kind of k_cube; whether exec and adjoint run it on tiling T.
+constexpr int kKindCube = 7;
+bool cube_persistent(const spinsum_plan_s& P, const Tiling& T);
 
 // Implemented in spinsum_plan.cpp
 spinsum_status build_tiling(const spinsum_plan_s& P, int n, int64_t ncubes,

@@ -242,8 +242,8 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
   }
   std::vector<spinsum_tile_t> cands;
   // the planner's own choice first: where it runs on tiles that no request
-  // names (spinsum_plan_info_t.rows_bl), winning keeps it
-  if (P->x_rows) cands.push_back(spinsum_tile_t{0, 1, 0, 1, 0, 0});
+  // names (spinsum_plan_info_t.sum_bl), winning keeps it
+  if (P->x_own) cands.push_back(spinsum_tile_t{0, 1, 0, 1, 0, 0});
   for (const spinsum_tile_t& sh : shapes) {
     spinsum_tile_t t = sh;
     t.lds_pad = 0;

@@ -1,5 +1,5 @@
 """Parity, on an MI355X, of the kernel for tile rows that start on any element
-(extents whose rows are not whole 16-byte chunks, spinsum_plan_info_t.rows_bl):
+(extents whose rows are not whole 16-byte chunks, spinsum_plan_info_t.sum_bl):
 bitwise against the register kernel on an explicit tile (both form every
 output as the same chain of fused multiply-adds) and against the oracle.  The
 extents leave every possible end of a row, a last block of one element, and
@@ -59,10 +59,10 @@ def test_rows_kernel_against_register_kernel_and_oracle(case, flags):
     for sparse in (False, True):
         stages = stages_of(d, sparse)
         p = ss.spinsum_plan(shape, gf, d, stages, dtype=dtype, inplace=inplace, flags=flags)
-        assert ss.spinsum_plan_get_info(p)["rows_bl"] > 0
+        assert ss.spinsum_plan_get_info(p)["sum_bl"] > 0
         q = ss.spinsum_plan(shape, gf, d, stages, dtype=dtype, inplace=inplace, flags=flags)
         ss.spinsum_plan_set_tile(q, bl, variant=ss.SPINSUM_VARIANT_REG_ONESHOT)
-        assert ss.spinsum_plan_get_info(q)["rows_bl"] == 0
+        assert ss.spinsum_plan_get_info(q)["sum_bl"] == 0
         x = workloads.uniform(shape, 8100 + case, device=DEV, dtype=dtype)
         if sparse:
             x.view(-1)[5] = float("inf")
@@ -91,7 +91,7 @@ def test_rows_kernel_chained_stages():
     want = oracle.spinsum_chain(x.cpu().numpy(), workloads.FACTORED_PIJ_PJK, 1, 3)
     for flags in (ss.SPINSUM_FLAG_CHAIN_STAGES, ss.SPINSUM_FLAG_MULTI_PASS):
         p = ss.spinsum_plan(shape, 1, 3, workloads.FACTORED_PIJ_PJK, flags=flags)
-        assert ss.spinsum_plan_get_info(p)["rows_bl"] > 0
+        assert ss.spinsum_plan_get_info(p)["sum_bl"] > 0
         y = torch.empty_like(x)
         ss.spinsum_exec(p, x, y)
         torch.cuda.synchronize()

@@ -705,7 +705,7 @@ def test_lds_pipeline_variant_needs_two_buffers():
     assert ss.spinsum_plan_get_info(r)["variant"] == ss.SPINSUM_VARIANT_REG_ONESHOT
 
 
-@pytest.mark.parametrize("shape,gf,d,dtype,rows_bl", [
+@pytest.mark.parametrize("shape,gf,d,dtype,sum_bl", [
     ((3, 33, 33, 33), 1, 3, "f64", 8), ((2, 35, 35, 35), 1, 3, "f64", 8),
     ((2, 33, 33, 33), 1, 3, "f32", 8), ((2, 34, 34, 34), 1, 3, "f32", 8),
     ((2, 35, 35, 35), 1, 3, "f32", 8), ((2, 27, 27, 27, 3), 1, 3, "f64", 6),
@@ -715,18 +715,40 @@ def test_lds_pipeline_variant_needs_two_buffers():
     ((1, 21, 21, 21, 21), 1, 4, "f64", 0), ((2, 34, 34, 34), 1, 3, "f64", 0),
     ((2, 25, 25, 25), 1, 3, "f64", 0),
 ])
-def test_rows_tiling_rule(shape, gf, d, dtype, rows_bl):
+def test_rows_tiling_rule(shape, gf, d, dtype, sum_bl):
     """Where the planner's tile has no rows of whole 16-byte chunks, exec runs
     on tiles of their own whose rows start on any element; the checker
     replays both tilings."""
     terms = [[(p, 1.0) for p in itertools.permutations(range(d))]]
     p = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype, flags=HOST)
-    assert ss.spinsum_plan_get_info(p)["rows_bl"] == rows_bl
+    assert ss.spinsum_plan_get_info(p)["sum_bl"] == sum_bl
     ok, why = ss.spinsum_plan_check_ownership(p)
     assert ok, why
-    if rows_bl:
+    if sum_bl:
         q = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype,
                             flags=HOST | ss.SPINSUM_FLAG_NO_DIRECT_LDS)
-        assert ss.spinsum_plan_get_info(q)["rows_bl"] == 0
+        assert ss.spinsum_plan_get_info(q)["sum_bl"] == 0
         ss.spinsum_plan_set_tile(p, 3, variant=ss.SPINSUM_VARIANT_REG_ONESHOT)
-        assert ss.spinsum_plan_get_info(p)["rows_bl"] == 0
+        assert ss.spinsum_plan_get_info(p)["sum_bl"] == 0
+
+
+def test_whole_cube_sum_rule():
+    """Cubes that fit a CU are summed whole where the planner's tile has rows
+    of part lines and there are two cubes per CU; the tile itself stays what
+    it was (the coefficient gradient and packing use it)."""
+    cfg3, cfg2 = [workloads.CONFIG_3D_ALPHA], [[((0, 1), 2.0), ((1, 0), -1.0)]]
+    def own(shape, gf, d, terms, dtype="f64", inplace=True, flags=0):
+        p = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype, inplace=inplace, flags=HOST | flags)
+        ok, why = ss.spinsum_plan_check_ownership(p)
+        assert ok, why
+        i = ss.spinsum_plan_get_info(p)
+        return i["bl"], i["sum_bl"]
+    assert own((512, 24, 24, 24), 1, 3, cfg3) == (8, 24)
+    assert own((511, 24, 24, 24), 1, 3, cfg3) == (8, 0)             # too few cubes
+    assert own((512, 24, 24, 24), 1, 3, cfg3, inplace=False) == (24, 0)
+    assert own((600, 120, 120), 1, 2, cfg2) == (40, 120)
+    assert own((600, 12, 12, 12, 8), 1, 3, cfg3) == (4, 0)          # tiles of whole lines
+    assert own((600, 32, 32, 32), 1, 3, cfg3) == (8, 0)             # does not fit
+    assert own((600, 32, 32, 32), 1, 3, cfg3, dtype="f32") == (16, 0)  # packed orbits
+    assert own((600, 12, 12, 12, 12), 1, 4, [workloads.antisymmetrizer(4)]) == (6, 0)
+    assert own((512, 24, 24, 24), 1, 3, cfg3, flags=ss.SPINSUM_FLAG_NO_XCD_REMAP) == (8, 0)
