@@ -110,27 +110,16 @@ static void lds_strides(int d, int bl, int pad, int inner, int32_t* lst, int32_t
   *ts = (int32_t)t;
 }
 
-// Largest number of distinct tiles in one orbit for nb blocks per axis.
+// Largest number of distinct tiles in one orbit for nb blocks per axis: the
+// arrangements of a block tuple whose d entries take the nb values as evenly
+// as they can.
 static int max_orbit_tiles(const SymGroup& G, int nb) {
-  const int d = G.d;
-  std::vector<int> B(d, 0);
-  int best = 0;
-  while (true) {
-    std::vector<std::vector<int>> tl;
-    for (int r = 0; r < G.df; ++r) {
-      std::vector<int> t(d);
-      for (int m = 0; m < d; ++m) t[m] = B[G.p[r][m]];
-      if (std::find(tl.begin(), tl.end(), t) == tl.end()) tl.push_back(t);
-    }
-    best = std::max(best, (int)tl.size());
-    if (best == G.df) break;
-    int m = d - 1;
-    while (m >= 0 && B[m] == nb - 1) --m;
-    if (m < 0) break;
-    B[m]++;
-    for (int j = m + 1; j < d; ++j) B[j] = B[m];
+  int r = G.df;
+  for (int b = 0; b < std::min(nb, G.d); ++b) {
+    const int count = G.d / nb + (b < G.d % nb ? 1 : 0);
+    for (int k = 2; k <= count; ++k) r /= k;
   }
-  return best;
+  return r;
 }
 
 // Element orbits of a whole N^d cube under the plan's group (Burnside: the
@@ -172,24 +161,21 @@ static int64_t rep_bank_cost(const uint32_t* reps, size_t cnt, const SymGroup& G
   const int d = G.d;
   const int words = esz / 4;
   int64_t cost = 0;
-  std::vector<uint32_t> w;
   for (size_t g0 = 0; g0 < cnt; g0 += 64) {
     const size_t g1 = std::min(cnt, g0 + 64);
     for (int r = 0; r < G.df; ++r) {
-      w.clear();
+      // (the lanes' words are all different: each holds another element)
+      int hist[64] = {0};
+      const int* p = G.p[r].data();
       for (size_t i = g0; i < g1; ++i) {
-        int64_t a = 0;
-        for (int m = 0; m < d; ++m) a += (int64_t)((reps[i] >> (8 * G.p[r][m])) & 255u) * lst[m];
-        for (int k = 0; k < words; ++k) w.push_back((uint32_t)(a * words + k));
+        uint32_t a = 0;
+        for (int m = 0; m < d; ++m) a += ((reps[i] >> (8 * p[m])) & 255u) * (uint32_t)lst[m];
+        for (int k = 0; k < words; ++k) ++hist[(a * (uint32_t)words + (uint32_t)k) % 64];
       }
-      std::sort(w.begin(), w.end());
-      w.erase(std::unique(w.begin(), w.end()), w.end());
-      for (int banks : {64, 32}) {
-        int hist[64] = {0};
-        int worst = 0;
-        for (uint32_t x : w) worst = std::max(worst, ++hist[x % banks]);
-        cost += worst;
-      }
+      int worst64 = 0, worst32 = 0;
+      for (int k = 0; k < 64; ++k) worst64 = std::max(worst64, hist[k]);
+      for (int k = 0; k < 32; ++k) worst32 = std::max(worst32, hist[k] + hist[k + 32]);
+      cost += worst64 + worst32;
     }
   }
   return cost;
@@ -210,14 +196,17 @@ static bool order_reps_for_banks(std::vector<uint32_t>& reps, size_t off, const 
   const int d = G.d;
   const size_t cnt = reps.size() - off;
   if (cnt <= 1 || e <= 1) return false;
-  std::vector<uint32_t> alt(reps.begin() + off, reps.end());
+  // (a stable counting sort by the class)
   auto cls = [&](uint32_t pk) {
     int c = (int)((pk >> (8 * (d - 1))) & 255u);
     for (int m = 0; m + 1 < d; ++m) c -= (int)((pk >> (8 * m)) & 255u);
     return ((c % e) + e) % e;
   };
-  std::stable_sort(alt.begin(), alt.end(),
-                   [&](uint32_t x, uint32_t y) { return cls(x) < cls(y); });
+  std::vector<size_t> at((size_t)e + 1, 0);
+  for (size_t i = 0; i < cnt; ++i) ++at[(size_t)cls(reps[off + i]) + 1];
+  for (int k = 0; k < e; ++k) at[(size_t)k + 1] += at[(size_t)k];
+  std::vector<uint32_t> alt(cnt);
+  for (size_t i = 0; i < cnt; ++i) alt[at[(size_t)cls(reps[off + i])]++] = reps[off + i];
   if (rep_bank_cost(alt.data(), cnt, G, lst, esz) >=
       rep_bank_cost(reps.data() + off, cnt, G, lst, esz))
     return false;
@@ -445,21 +434,18 @@ spinsum_status build_tiling(const spinsum_plan_s& P, int n, int64_t ncubes,
     if (ri == rep_index.end()) {
       int off = (int)T.reps.size();
       std::vector<int> l(d, 0);
-      int64_t box = 1;
-      for (int m = 0; m < d; ++m) box *= extB[m];
-      for (int64_t e = 0; e < box; ++e) {
-        int64_t rem = e;
-        for (int m = d - 1; m >= 0; --m) {
-          l[m] = (int)(rem % extB[m]);
-          rem /= extB[m];
-        }
-        bool ok = true;
-        for (int m = 0; m + 1 < d; ++m)
-          if (B[m] == B[m + 1] && l[m] > l[m + 1]) ok = false;
-        if (!ok) continue;
+      // in lexicographic order, the next one found by an odometer whose
+      // wheels start at their left neighbour inside a run of equal blocks
+      auto first = [&](int m) { return m > 0 && B[m - 1] == B[m] ? l[m - 1] : 0; };
+      for (;;) {
         uint32_t pk = 0;
         for (int m = 0; m < d; ++m) pk |= (uint32_t)l[m] << (8 * m);
         T.reps.push_back(pk);
+        int m = d - 1;
+        while (m >= 0 && l[m] == extB[m] - 1) --m;
+        if (m < 0) break;
+        ++l[m];
+        for (int j = m + 1; j < d; ++j) l[j] = first(j);
       }
       T.reps_lex.insert(T.reps_lex.end(), T.reps.begin() + off, T.reps.end());
       if (inner == 1 && order_reps_for_banks(T.reps, (size_t)off, G, g.lst, elem_size(P), bl))
@@ -599,29 +585,59 @@ void free_device(spinsum_plan_s* P) {
                    &P->d_items,     &P->d_grad_part,   &P->d_cg_orbits, &P->d_cg_reps,
                    &P->d_reps_lex,  &P->d_pk_orbits,   &P->d_pk_reps,   &P->d_x_orbits,
                    &P->d_x_reps};
-  for (void** p : ptrs) {
-    if (*p) (void)hipFree(*p);
-    *p = nullptr;
-  }
+  for (void** p : ptrs) *p = nullptr;
+  if (P->d_tables) (void)hipFree(P->d_tables);
+  P->d_tables = nullptr;
   P->has_dev = false;
   P->cg_pack = false;
   P->pk_own = false;
 }
 
-template <typename V>
-static spinsum_status upload(spinsum_plan_s* P, void** dst, const V* src, size_t count) {
-  size_t bytes = std::max<size_t>(sizeof(V), count * sizeof(V));
-  hipError_t e = hipMalloc(dst, bytes);
+// The plan's device tables: one allocation for all of them (a training step
+// makes a plan per call, and every allocation, copy and free is a trip
+// through the runtime), each on a 256-byte boundary.
+struct Uploads {
+  struct Part {
+    void** dst;
+    const void* src;  // nullptr: memory only
+    size_t bytes;
+    size_t at;
+  };
+  std::vector<Part> parts;
+  size_t total = 0;
+  template <typename V>
+  void add(void** dst, const V* src, size_t count) {
+    const size_t bytes = std::max<size_t>(sizeof(V), count * sizeof(V));
+    parts.push_back({dst, count ? src : nullptr, bytes, total});
+    total += (bytes + 255) / 256 * 256;
+  }
+};
+
+static spinsum_status upload(spinsum_plan_s* P, const Uploads& U) {
+  hipError_t e = hipMalloc(&P->d_tables, std::max<size_t>(256, U.total));
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    *dst = nullptr;
+    P->d_tables = nullptr;
     P->last_hip_error = (int)e;
     return e == hipErrorOutOfMemory ? SPINSUM_ERR_OUT_OF_MEMORY : SPINSUM_ERR_HIP;
   }
-  if (count) {
-    e = hipMemcpy(*dst, src, count * sizeof(V), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(P, e);
+  char* base = reinterpret_cast<char*>(P->d_tables);
+  // small tables in one copy, large ones (index pairs) each from its place
+  std::vector<char> stage;
+  size_t copied = 0;
+  for (const Uploads::Part& p : U.parts)
+    if (p.src) copied = p.at + p.bytes;
+  if (copied <= ((size_t)4 << 20)) {
+    stage.resize(copied);
+    for (const Uploads::Part& p : U.parts)
+      if (p.src) std::memcpy(stage.data() + p.at, p.src, p.bytes);
+    if (copied) e = hipMemcpy(base, stage.data(), copied, hipMemcpyHostToDevice);
+  } else {
+    for (const Uploads::Part& p : U.parts)
+      if (p.src && e == hipSuccess) e = hipMemcpy(base + p.at, p.src, p.bytes, hipMemcpyHostToDevice);
   }
+  if (e != hipSuccess) return hip_fail(P, e);
+  for (const Uploads::Part& p : U.parts) *p.dst = base + p.at;
   return SPINSUM_OK;
 }
 
@@ -643,10 +659,10 @@ static bool cgrad_split_ok(const spinsum_plan_s& P) {
   return lds <= P.lds_limit;
 }
 
-static spinsum_status build_cgrad_tiling(spinsum_plan_s* P) {
+static void build_cgrad_tiling(spinsum_plan_s* P) {
   const Tiling& T = P->T;
   const int esz = elem_size(*P);
-  if (P->cg_split) return SPINSUM_OK;  // one tile buffer: no packed tiling needed
+  if (P->cg_split) return;  // one tile buffer: no packed tiling needed
   auto cg_lds = [&](const Tiling& X) {
     return 2 * ((X.lds_elems * esz + 15) / 16 * 16) + (int64_t)X.max_rep_cnt * 4;
   };
@@ -658,6 +674,9 @@ static spinsum_status build_cgrad_tiling(spinsum_plan_s* P) {
     // the largest edge with whole 16-byte chunks per row whose tile orbits,
     // both tensors, fit half a CU's LDS
     for (int bl = P->n - 1; bl >= 1; --bl) {
+      // (the tiles of both tensors alone, before any table is built)
+      const int tiles = max_orbit_tiles(P->G, (P->n + bl - 1) / bl);
+      if (2 * tiles * ipow(bl, P->d) * P->inner * esz > P->lds_limit / 2) continue;
       spinsum_tile_t t = P->tile;
       t.bl = bl;
       t.cubes_per_wg = 1;
@@ -666,32 +685,23 @@ static spinsum_status build_cgrad_tiling(spinsum_plan_s* P) {
       Tiling Tc;
       if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) continue;
       if (!Tc.fits || (int64_t)Tc.vw * esz != 16 || cg_lds(Tc) > P->lds_limit / 2) continue;
-      spinsum_status st = upload(P, &P->d_cg_orbits, Tc.groups.data(), Tc.groups.size());
-      if (st != SPINSUM_OK) return st;
-      st = upload(P, &P->d_cg_reps, Tc.reps.data(), Tc.reps.size());
-      if (st != SPINSUM_OK) return st;
       P->Tc = std::move(Tc);
       P->cg_pack = true;
-      return SPINSUM_OK;
+      return;
     }
-    return SPINSUM_OK;
+    return;
   }
   if (P->pair || P->batched || T.g.bl >= T.g.n || T.orbits.size() < 2 ||
       T.groups.size() != T.orbits.size() || P->tile.lds_pad != 0)
-    return SPINSUM_OK;
-  if (P->lds_limit / std::max<int64_t>(1, cg_lds(T)) >= 4) return SPINSUM_OK;
+    return;
+  if (P->lds_limit / std::max<int64_t>(1, cg_lds(T)) >= 4) return;
   spinsum_tile_t t = P->tile;
   t.item_tiles = T.max_orbit_tiles;
   Tiling Tc;
-  if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) return SPINSUM_OK;
-  if (cg_lds(Tc) > P->lds_limit || Tc.vw != T.vw) return SPINSUM_OK;
-  spinsum_status st = upload(P, &P->d_cg_orbits, Tc.groups.data(), Tc.groups.size());
-  if (st != SPINSUM_OK) return st;
-  st = upload(P, &P->d_cg_reps, Tc.reps.data(), Tc.reps.size());
-  if (st != SPINSUM_OK) return st;
+  if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) return;
+  if (cg_lds(Tc) > P->lds_limit || Tc.vw != T.vw) return;
   P->Tc = std::move(Tc);
   P->cg_pack = true;
-  return SPINSUM_OK;
 }
 
 // Store mode (measured on MI355X): non-temporal stores stream whole lines
@@ -769,7 +779,10 @@ static void choose_unpack_tiling(spinsum_plan_s* P) {
     t.item_tiles = 0;
     t.threads = 0;
     Tiling Tu;
-    if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tu) != SPINSUM_OK) continue;
+    if (bl == P->n && T.g.bl == P->n)
+      Tu = T;  // (one whole cube per item already)
+    else if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tu) != SPINSUM_OK)
+      continue;
     if (!Tu.fits || lds_of(Tu) > P->lds_limit) continue;
     if (bl < P->n && (int64_t)Tu.vw * esz != 16) continue;  // rows of whole 16-byte chunks
     const int64_t per_cu = std::max<int64_t>(1, P->lds_limit / std::max<int64_t>(1, lds_of(Tu)));
@@ -970,58 +983,48 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
   choose_unpack_tiling(P);
   choose_unpack_gather(P);
   if (P->flags & SPINSUM_FLAG_HOST_ONLY) return SPINSUM_OK;
-  spinsum_status st;
+  Uploads U;
   // coefficient vectors in the storage type: forward | adjoint | stages | adjoint stages
   std::vector<double> all;
   all.insert(all.end(), P->M.begin(), P->M.end());
   all.insert(all.end(), P->MT.begin(), P->MT.end());
   all.insert(all.end(), P->SM.begin(), P->SM.end());
   all.insert(all.end(), P->SMT.begin(), P->SMT.end());
-  if (P->dtype == SPINSUM_F32) {
-    std::vector<float> f(all.begin(), all.end());
-    st = upload(P, &P->d_mats, f.data(), f.size());
-  } else {
-    st = upload(P, &P->d_mats, all.data(), all.size());
-  }
-  if (st != SPINSUM_OK) return st;
+  const std::vector<float> f(all.begin(), all.end());
+  if (P->dtype == SPINSUM_F32)
+    U.add(&P->d_mats, f.data(), f.size());
+  else
+    U.add(&P->d_mats, all.data(), all.size());
+  std::vector<GroupDev> groups;
+  std::vector<uint32_t> reps;
   if (P->pair) {
-    st = upload(P, &P->d_orbits, P->pair_orbits.data(), P->pair_orbits.size());
-    if (st != SPINSUM_OK) return st;
-    st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
-    if (st != SPINSUM_OK) return st;
+    U.add(&P->d_orbits, P->pair_orbits.data(), P->pair_orbits.size());
+    U.add(&P->d_reps, P->T.reps.data(), P->T.reps.size());
   } else if (!P->batched) {
     // (with k_rows nothing runs on T: the coefficient gradient and packing
     // refuse rows that are not whole 16-byte chunks)
     if (!(P->x_own && P->Tx.any_rows)) {
-      st = upload(P, &P->d_orbits, P->T.groups.data(), P->T.groups.size());
-      if (st != SPINSUM_OK) return st;
-      st = upload(P, &P->d_reps, P->T.reps.data(), P->T.reps.size());
-      if (st != SPINSUM_OK) return st;
-      if (!P->T.reps_lex.empty()) {
-        st = upload(P, &P->d_reps_lex, P->T.reps_lex.data(), P->T.reps_lex.size());
-        if (st != SPINSUM_OK) return st;
-      }
+      U.add(&P->d_orbits, P->T.groups.data(), P->T.groups.size());
+      U.add(&P->d_reps, P->T.reps.data(), P->T.reps.size());
+      if (!P->T.reps_lex.empty()) U.add(&P->d_reps_lex, P->T.reps_lex.data(), P->T.reps_lex.size());
     }
     if (P->x_own) {
-      st = upload(P, &P->d_x_orbits, P->Tx.groups.data(), P->Tx.groups.size());
-      if (st != SPINSUM_OK) return st;
-      st = upload(P, &P->d_x_reps, P->Tx.reps.data(), P->Tx.reps.size());
-      if (st != SPINSUM_OK) return st;
+      U.add(&P->d_x_orbits, P->Tx.groups.data(), P->Tx.groups.size());
+      U.add(&P->d_x_reps, P->Tx.reps.data(), P->Tx.reps.size());
     }
-    std::vector<double> part((size_t)kGradSlots * P->G.df, 0.0);
-    st = upload(P, &P->d_grad_part, part.data(), part.size());
-    if (st != SPINSUM_OK) return st;
-    st = build_cgrad_tiling(P);
-    if (st != SPINSUM_OK) return st;
+    build_cgrad_tiling(P);
+    if (P->cg_pack) {
+      U.add(&P->d_cg_orbits, P->Tc.groups.data(), P->Tc.groups.size());
+      U.add(&P->d_cg_reps, P->Tc.reps.data(), P->Tc.reps.size());
+    }
     if (P->pk_own) {
-      st = upload(P, &P->d_pk_orbits, P->Tu.groups.data(), P->Tu.groups.size());
-      if (st != SPINSUM_OK) return st;
-      st = upload(P, &P->d_pk_reps, P->Tu.reps.data(), P->Tu.reps.size());
-      if (st != SPINSUM_OK) return st;
+      U.add(&P->d_pk_orbits, P->Tu.groups.data(), P->Tu.groups.size());
+      U.add(&P->d_pk_reps, P->Tu.reps.data(), P->Tu.reps.size());
     }
+    // last, and not copied: the gradient clears its partial sums itself
+    U.add(&P->d_grad_part, (const double*)nullptr, 0);
+    U.total += (size_t)kGradSlots * P->G.df * sizeof(double);
   } else {
-    std::vector<GroupDev> groups;
-    std::vector<uint32_t> reps;
     for (const Tiling& t : P->btil) {
       int roff = (int)reps.size();
       for (GroupDev gd : t.groups) {
@@ -1030,15 +1033,13 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
       }
       reps.insert(reps.end(), t.reps.begin(), t.reps.end());
     }
-    st = upload(P, &P->d_orbits, groups.data(), groups.size());
-    if (st != SPINSUM_OK) return st;
-    st = upload(P, &P->d_reps, reps.data(), reps.size());
-    if (st != SPINSUM_OK) return st;
-    st = upload(P, &P->d_blocks, P->blocks.data(), P->blocks.size());
-    if (st != SPINSUM_OK) return st;
-    st = upload(P, &P->d_items, P->items.data(), P->items.size());
-    if (st != SPINSUM_OK) return st;
+    U.add(&P->d_orbits, groups.data(), groups.size());
+    U.add(&P->d_reps, reps.data(), reps.size());
+    U.add(&P->d_blocks, P->blocks.data(), P->blocks.size());
+    U.add(&P->d_items, P->items.data(), P->items.size());
   }
+  spinsum_status st = upload(P, U);
+  if (st != SPINSUM_OK) return st;
   P->has_dev = true;
   return cache_occupancy(P);
 }

@@ -154,6 +154,7 @@ struct spinsum_plan_s {
   int device = -1;
   int num_cus = 256;
   int lds_limit = spinsum::kMaxLdsBytes;
+  void* d_tables = nullptr;  // the allocation that holds the tables below
   void* d_orbits = nullptr;
   void* d_reps = nullptr;
   void* d_reps_lex = nullptr;  // Tiling::reps_lex on the device, if any
