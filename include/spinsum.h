@@ -326,6 +326,16 @@ spinsum_status spinsum_adjoint(spinsum_plan_t plan, const void* grad_out, void* 
 spinsum_status spinsum_coef_grad(spinsum_plan_t plan, const void* x, const void* g,
                                  double* grad, void* stream);
 
+/* Both gradients of a backward pass: gx = S^T g (spinsum_adjoint) and grad
+ * (spinsum_coef_grad), from one read of g where the plan's kernels allow it
+ * (d <= 3, the operator moves every axis of the group, no stage chaining):
+ * three passes over memory instead of four.  Arguments, restrictions and
+ * errors as for the two functions; in-place plans need gx == g; x must not
+ * overlap gx.  Calls on one plan must not overlap.  Asynchronous on
+ * `stream`. */
+spinsum_status spinsum_adjoint_coef_grad(spinsum_plan_t plan, const void* x, const void* g,
+                                         void* gx, double* grad, void* stream);
+
 /* Unpacking (the paper names tensor unpacking, Sec. 1 and Sec. 7, as another
  * sum of permutations; its layout is not fixed there).  A packed tensor
  * holds one value per strictly increasing tuple i_0 < ... < i_{d-1} of the

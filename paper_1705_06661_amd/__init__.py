@@ -127,6 +127,7 @@ _c_exec = _decl("spinsum_exec", [_vp, _vp, _vp, _vp])
 _c_exec_batched = _decl("spinsum_exec_batched", [_vp, _vp, _vp, _vp])
 _c_adjoint = _decl("spinsum_adjoint", [_vp, _vp, _vp, _vp])
 _c_coef_grad = _decl("spinsum_coef_grad", [_vp, _vp, _vp, _vp, _vp])
+_c_adjoint_coef_grad = _decl("spinsum_adjoint_coef_grad", [_vp, _vp, _vp, _vp, _vp, _vp])
 _c_coef_grad_noalloc = _decl("spinsum_coef_grad_noalloc", [_vp, _vp, _vp, _vp, _vp])
 _c_coef_grad_stages = _decl("spinsum_coef_grad_stages", [_vp, _vp, _vp, _vp, _vp, _vp, _vp])
 _c_unpack = _decl("spinsum_unpack", [_vp, _vp, _vp, _vp])
@@ -145,6 +146,7 @@ _c_version = _decl("spinsum_version", [], ctypes.c_char_p)
 EXPORTED = ["spinsum_plan", "spinsum_plan_batched", "spinsum_plan_set_tile",
             "spinsum_plan_get_info", "spinsum_plan_expanded", "spinsum_plan_check_ownership",
             "spinsum_exec", "spinsum_exec_batched", "spinsum_adjoint", "spinsum_coef_grad",
+            "spinsum_adjoint_coef_grad",
             "spinsum_coef_grad_noalloc", "spinsum_coef_grad_stages", "spinsum_unpack",
             "spinsum_pack",
             "spinsum_graph_create",
@@ -346,6 +348,20 @@ def spinsum_coef_grad(plan: Plan, x: torch.Tensor, g: torch.Tensor, stream=None)
     b = _tensor_ptr(g, plan, plan.shape, "g")
     out = torch.empty(math.factorial(plan.d), dtype=torch.float64, device=x.device)
     _check(_c_coef_grad(plan._h, a, b, out.data_ptr(), _stream(stream)), "spinsum_coef_grad", plan)
+    return out
+
+
+def spinsum_adjoint_coef_grad(plan: Plan, x: torch.Tensor, g: torch.Tensor, gx: torch.Tensor,
+                              stream=None) -> torch.Tensor:
+    """gx = S^T g and, returned, <g, pi_r(x)> for every permutation r (see
+    spinsum_adjoint and spinsum_coef_grad), from one read of g where the
+    plan allows it."""
+    a = _tensor_ptr(x, plan, plan.shape, "x")
+    b = _tensor_ptr(g, plan, plan.shape, "g")
+    c = _tensor_ptr(gx, plan, plan.shape, "gx")
+    out = torch.empty(math.factorial(plan.d), dtype=torch.float64, device=x.device)
+    _check(_c_adjoint_coef_grad(plan._h, a, b, c, out.data_ptr(), _stream(stream)),
+           "spinsum_adjoint_coef_grad", plan)
     return out
 
 
@@ -575,13 +591,15 @@ class SpinSumCoefFunction(torch.autograd.Function):
         (x,) = ctx.saved_tensors
         plan = ctx.plan
         g = g.contiguous()
-        gx = None
-        if ctx.needs_input_grad[0]:
-            gx = torch.empty_like(g)
-            spinsum_adjoint(plan, g, gx)
+        gx = torch.empty_like(g) if ctx.needs_input_grad[0] else None
         ga = None
+        if gx is not None and not ctx.needs_input_grad[1]:
+            spinsum_adjoint(plan, g, gx)
         if ctx.needs_input_grad[1]:
-            c = spinsum_coef_grad(plan, x.contiguous(), g)
+            if gx is not None:
+                c = spinsum_adjoint_coef_grad(plan, x.contiguous(), g, gx)
+            else:
+                c = spinsum_coef_grad(plan, x.contiguous(), g)
             d = len(ctx.perms[0])
             rank = {p: r for r, p in enumerate(itertools.permutations(range(d)))}
             ga = torch.stack([c[rank[p]] for p in ctx.perms]).to(x.dtype)

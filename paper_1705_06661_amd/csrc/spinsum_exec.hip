@@ -73,15 +73,15 @@ const void* pick_gather(int d, bool persist) {
 }
 
 template <typename T>
-const void* pick_cgrad(int d, bool split) {
+const void* pick_cgrad(int d, bool split, bool adj) {
   if constexpr (sizeof(T) == 8) {
-    if (d == 2) return pick_cgrad_f64_d2(split);
-    if (d == 3) return pick_cgrad_f64_d3(split);
-    return pick_cgrad_f64_d4(split);
+    if (d == 2) return pick_cgrad_f64_d2(split, adj);
+    if (d == 3) return pick_cgrad_f64_d3(split, adj);
+    return pick_cgrad_f64_d4(split, adj);
   } else {
-    if (d == 2) return pick_cgrad_f32_d2(split);
-    if (d == 3) return pick_cgrad_f32_d3(split);
-    return pick_cgrad_f32_d4(split);
+    if (d == 2) return pick_cgrad_f32_d2(split, adj);
+    if (d == 3) return pick_cgrad_f32_d3(split, adj);
+    return pick_cgrad_f32_d4(split, adj);
   }
 }
 
@@ -463,13 +463,13 @@ namespace spinsum {
 namespace {
 
 template <typename T>
-spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, double* grad,
+spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, void* gx, double* grad,
                             double* part, hipStream_t stream) {
   // one tile buffer on the plan's tiling where it allows (k_cgrad_split),
   // else both tensors in LDS on the packed tiling where the plan has one
   // (see build_cgrad_tiling)
-  const bool split = P->cg_split;
-  const bool packed = P->cg_pack && !split;
+  const bool split = P->cg_split || P->cg_own_split;
+  const bool packed = P->cg_pack && !P->cg_split;
   const Tiling& Tl = packed ? P->Tc : P->T;
   CGradArgs<T> a;
   std::memset(&a, 0, sizeof(a));
@@ -484,11 +484,26 @@ spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, dou
   const int df = P->G.df;
   // LDS: x tiles | gradient tiles (k_cgrad only) | representative lists;
   // the partial sums of the waves reuse it at the end
-  const size_t shmem = std::max<size_t>((split ? 1 : 2) * (size_t)a.lds_tile_bytes +
-                                            (size_t)Tl.max_rep_cnt * 4,
-                                        (size_t)(kThreads / 64) * df * sizeof(double));
+  const bool adj = gx != nullptr;
+  const size_t lds = (split ? 1 : 2) * (size_t)a.lds_tile_bytes + (size_t)Tl.max_rep_cnt * 4;
+  // whole cubes of which a CU holds one pair: 512 threads (both gradients of
+  // 24^3 FP32 468 against 500 us, 120^2 FP32 420 against 487, 18^3 FP64 874
+  // against 892; 20^3 FP64 821 against 798); otherwise more workgroups serve
+  // better (16^3 FP32 315 against 405 us)
+  const bool wide = P->d <= 3 && !split && Tl.g.bl == Tl.g.n && 2 * (int64_t)lds > P->lds_limit;
+  const int threads = wide ? 2 * kThreads : kThreads;
+  const size_t red = (size_t)(threads / 64) * df * sizeof(double);
+  size_t shmem = std::max(lds, red);
+  if (adj) {
+    a.gx = reinterpret_cast<T*>(gx);
+    const CoefSel sel = coef_sel(P, true);
+    a.coef = reinterpret_cast<const T*>(P->d_mats) + sel.offset;
+    a.sparse = sel.sparse;
+    a.nts = Tl.nts;
+    if (split) shmem = (size_t)a.lds_tile_bytes + std::max<size_t>((size_t)Tl.max_rep_cnt * 4, red);
+  }
   if ((int64_t)shmem > P->lds_limit) return SPINSUM_ERR_UNSUPPORTED;
-  const void* k = pick_cgrad<T>(P->d, split);
+  const void* k = pick_cgrad<T>(P->d, split, adj);
   spinsum_status st = prepare_kernel(P, k, shmem);
   if (st != SPINSUM_OK) return st;
   hipLaunchKernelGGL(k_zero_f64, dim3(64), dim3(kThreads), 0, stream, a.grad, kGradSlots * df);
@@ -503,7 +518,7 @@ spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, dou
     grid = a.xcd_per * 8;
   }
   void* kargs[] = {&a};
-  e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(kThreads), kargs, shmem, stream);
+  e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(threads), kargs, shmem, stream);
   if (e != hipSuccess) return hip_error(P, e);
   hipLaunchKernelGGL(k_grad_reduce, dim3(df), dim3(kThreads), 0, stream,
                      (const double*)a.grad, grad, df);
@@ -548,10 +563,11 @@ spinsum_status scratch_on_device(spinsum_plan_s* P, double** out) {
   return SPINSUM_OK;
 }
 
-// spinsum_coef_grad with the partial sums in `part` (kGradSlots x d!
-// doubles) or, for part == nullptr, in this device's `scratch`.
+// spinsum_coef_grad with the partial sums in the plan's buffer or, with
+// use_scratch, in this device's `scratch`; with gx also the adjoint of g, in
+// the same launch (the caller has checked that the plan's kernels can).
 spinsum_status coef_grad_impl(spinsum_plan_s* P, const void* x, const void* g, double* grad,
-                              bool use_scratch, void* stream) {
+                              bool use_scratch, void* stream, void* gx = nullptr) {
   if (P == nullptr || P->batched || grad == nullptr) return SPINSUM_ERR_INVALID_ARG;
   if (!P->has_dev) return SPINSUM_ERR_NO_DEVICE;
   if (((uintptr_t)grad) & 7u) return SPINSUM_ERR_MISALIGNED;
@@ -579,8 +595,9 @@ spinsum_status coef_grad_impl(spinsum_plan_s* P, const void* x, const void* g, d
     st = scratch_on_device(P, &part);
     if (st != SPINSUM_OK) return st;
   }
-  if (P->dtype == SPINSUM_F32) return launch_cgrad<float>(P, x, g, grad, part, (hipStream_t)stream);
-  return launch_cgrad<double>(P, x, g, grad, part, (hipStream_t)stream);
+  if (P->dtype == SPINSUM_F32)
+    return launch_cgrad<float>(P, x, g, gx, grad, part, (hipStream_t)stream);
+  return launch_cgrad<double>(P, x, g, gx, grad, part, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -589,6 +606,29 @@ spinsum_status coef_grad_impl(spinsum_plan_s* P, const void* x, const void* g, d
 extern "C" spinsum_status spinsum_coef_grad(spinsum_plan_t P, const void* x, const void* g,
                                             double* grad, void* stream) {
   return coef_grad_impl(P, x, g, grad, false, stream);
+}
+
+extern "C" spinsum_status spinsum_adjoint_coef_grad(spinsum_plan_t P, const void* x, const void* g,
+                                                    void* gx, double* grad, void* stream) {
+  spinsum_status st = check_tensor_args(P, g, gx);
+  if (st != SPINSUM_OK) return st;
+  if (P->elems != 0) {
+    const uintptr_t bytes = (uintptr_t)P->elems * (uintptr_t)elem_size(*P);
+    const uintptr_t a = (uintptr_t)x, b = (uintptr_t)gx;
+    if (x != nullptr && a < b + bytes && b < a + bytes) return SPINSUM_ERR_ALIASING;
+  }
+  // one launch for both where the adjoint is the pre-multiplied operator of
+  // the whole group (d <= 3: a 4D orbit's 48 values and 24 sums leave no
+  // registers for the product), but not on the gradient's own tiles where
+  // they are ragged: whole cubes store better (22^3 FP64 957 us in two
+  // launches, 1303 in one)
+  const bool own_ragged = P->cg_pack && !P->cg_split && P->Tc.ragged != 0 && P->T.g.bl >= P->n;
+  if (P->elems != 0 && P->d <= 3 && P->sub == nullptr && !own_ragged &&
+      !(P->flags & (SPINSUM_FLAG_CHAIN_STAGES | SPINSUM_FLAG_MULTI_PASS)))
+    return coef_grad_impl(P, x, g, grad, false, stream, gx);
+  st = coef_grad_impl(P, x, g, grad, false, stream);  // (first: gx may be g)
+  if (st != SPINSUM_OK || P->elems == 0) return st;
+  return run(P, g, gx, (hipStream_t)stream, true);
 }
 
 extern "C" spinsum_status spinsum_coef_grad_stages(spinsum_plan_t P, const void* x, const void* g,

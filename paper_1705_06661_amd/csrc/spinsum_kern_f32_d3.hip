@@ -10,7 +10,7 @@ const void* pick_f32_d3(int kind, int vw, bool chain, bool nts, int maxc) {
 
 const void* pick_batched_f32_d3(int vw, bool persist) { return batched_kernel<float, 3>(vw, persist); }
 
-const void* pick_cgrad_f32_d3(bool split) { return cgrad_kernel<float, 3>(split); }
+const void* pick_cgrad_f32_d3(bool split, bool adj) { return cgrad_kernel<float, 3>(split, adj); }
 
 const void* pick_pack_f32_d3(bool pack, bool nts, bool persist) {
   return pack_kernel<float, 3>(pack, nts, persist);

@@ -646,8 +646,7 @@ static spinsum_status upload(spinsum_plan_s* P, const Uploads& U) {
 // workgroups onto a CU and the forward tiling has one orbit per item, it
 // gets a tiling of its own with consecutive orbits packed up to the largest
 // one (3D 32^3 slab: 3.51 -> 4.18 TB/s).
-static bool cgrad_split_ok(const spinsum_plan_s& P) {
-  const Tiling& T = P.T;
+static bool cgrad_split_ok(const spinsum_plan_s& P, const Tiling& T) {
   if (P.pair || P.batched || P.d > 3 || T.g.bl >= T.g.n || T.g.inner != 1) return false;
   if (P.tile.variant != SPINSUM_VARIANT_DIRECT_LDS || P.tile.lds_pad != 0) return false;
   if ((int64_t)T.vw * elem_size(P) != 16) return false;
@@ -659,6 +658,8 @@ static bool cgrad_split_ok(const spinsum_plan_s& P) {
   return lds <= P.lds_limit;
 }
 
+static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits);
+
 static void build_cgrad_tiling(spinsum_plan_s* P) {
   const Tiling& T = P->T;
   const int esz = elem_size(*P);
@@ -667,8 +668,30 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
     return 2 * ((X.lds_elems * esz + 15) / 16 * 16) + (int64_t)X.max_rep_cnt * 4;
   };
   const int vmax = max_vector_width(*P, (int64_t)std::max(1, P->n) * P->inner);
-  if (!P->pair && !P->batched && T.g.bl >= T.g.n && P->tile.lds_pad == 0 &&
-      cg_lds(T) > P->lds_limit) {
+  const bool whole = !P->pair && !P->batched && T.g.bl >= T.g.n && P->tile.lds_pad == 0;
+  if (whole && P->n > 0 && P->ncubes > 0 && cg_lds(T) > P->lds_limit) {
+    // whole cubes too large for both tensors: tiles for k_cgrad_split where
+    // it takes them (22^3 FP64 3.69 against 2.46 TB/s with both tensors'
+    // tiles in LDS, 24^3 4.62 against 3.14, 26^3 3.15 against 2.01, 100^2
+    // 4.95 against 2.51).  Cubes that fit stay whole (20^3 3.93 against 3.09).
+    for (int bl : {P->d == 2 ? 22 : 8, P->d == 2 ? 16 : 4}) {
+      if (bl >= P->n || ((int64_t)bl * esz) % 16 != 0) continue;
+      spinsum_tile_t t = P->tile;
+      t.bl = bl;
+      t.cubes_per_wg = 1;
+      t.item_tiles = 0;
+      t.threads = 0;
+      Tiling Tc;
+      if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK || !cgrad_split_ok(*P, Tc))
+        continue;
+      Tc.nts = choose_nts(*P, Tc, (int64_t)Tc.orbits.size());
+      P->Tc = std::move(Tc);
+      P->cg_pack = true;
+      P->cg_own_split = true;
+      return;
+    }
+  }
+  if (whole && cg_lds(T) > P->lds_limit) {
     // whole cubes too large for both tensors (out of place, FP64 cubes up
     // to a CU's LDS are summed whole): the gradient takes tiles of its own,
     // the largest edge with whole 16-byte chunks per row whose tile orbits,
@@ -685,7 +708,8 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
       Tiling Tc;
       if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) continue;
       if (!Tc.fits || (int64_t)Tc.vw * esz != 16 || cg_lds(Tc) > P->lds_limit / 2) continue;
-      P->Tc = std::move(Tc);
+      Tc.nts = choose_nts(*P, Tc, (int64_t)Tc.orbits.size());
+  P->Tc = std::move(Tc);
       P->cg_pack = true;
       return;
     }
@@ -700,6 +724,7 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
   Tiling Tc;
   if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) return;
   if (cg_lds(Tc) > P->lds_limit || Tc.vw != T.vw) return;
+  Tc.nts = choose_nts(*P, Tc, (int64_t)Tc.orbits.size());  // (the adjoint's, where it is formed too)
   P->Tc = std::move(Tc);
   P->cg_pack = true;
 }
@@ -979,7 +1004,8 @@ static void choose_rows_tiling(spinsum_plan_s* P) {
 
 spinsum_status upload_tables(spinsum_plan_s* P) {
   free_device(P);
-  P->cg_split = cgrad_split_ok(*P);
+  P->cg_split = cgrad_split_ok(*P, P->T);
+  P->cg_own_split = false;
   choose_unpack_tiling(P);
   choose_unpack_gather(P);
   if (P->flags & SPINSUM_FLAG_HOST_ONLY) return SPINSUM_OK;

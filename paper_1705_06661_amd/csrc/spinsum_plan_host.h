@@ -98,6 +98,7 @@ struct spinsum_plan_s {
   // tile's chunks in one pass of the workgroup, no inner runs, d <= 3
   // (decided with the tables, upload_tables)
   bool cg_split = false;
+  bool cg_own_split = false;  // Tc holds tiles for k_cgrad_split
   // The sum's own tiling (x_own): where the plan's default tiles have no rows
   // of whole 16-byte chunks, or part lines although a cube fits a CU, exec
   // and adjoint run on these tiles instead of T (choose_rows_tiling, k_rows;
