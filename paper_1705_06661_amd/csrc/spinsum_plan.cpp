@@ -1201,23 +1201,51 @@ static int64_t pair_lds_bytes(const spinsum_plan_s& P, int bl, int* vw_out) {
   return ((int64_t)tiles * ts * esz + 15) / 16 * 16 + ipow(bl, d) * 4;
 }
 
-// Default tile edge: the largest usable bl whose orbit fits 32 KiB of LDS,
-// else 64 KiB, else the LDS of a CU (the rules of the group form).
+// Default tile edge, the first of
+//  1. whole group cubes within 56 KiB of LDS an orbit;
+//  2. d > 2: rows of whole 64-byte halves of lines within 32 KiB, where
+//     ragged tiles cover at most 1.5 times the group;
+//  3. d > 2: the largest edge within 56 KiB that divides N, rows of at least 48
+//     bytes (FP32 32);
+//  4. the largest with rows of at least 32 bytes within 32 KiB, then 56 KiB;
+//  5. any usable edge within 32 KiB, 64 KiB or the LDS of a CU.
+// Measured, in place (GB/s): 10^3 FP64 whole 4811, 8^3 ragged 2015; 12^3 FP64
+// 6^3 4503, 8^3 3240; 12^3 FP32 whole 4830, 8^3 1746; 14^3 FP64 8^3 4439,
+// 10^3 3374; 20^3 FP64 10^3 4693, 8^3 3981 (out of place 3752 and 3976: FP64
+// part lines written by different items, so 3. stays within 32 KiB there);
+// 24^3 FP32 12^3 4451, 8^3 3959; 24^3 FP64 8^3 4884, 12^3 (83 KiB) 3974; 10^4
+// FP64 4^4 2380, 2^4 264.
 static spinsum_status choose_pair_tile(const spinsum_plan_s& P, spinsum_tile_t* tile) {
   const int64_t budget = P.lds_limit - 512;
-  for (int64_t cap : {(int64_t)32 * 1024, (int64_t)64 * 1024, budget}) {
-    for (int bl = std::min(P.n, 255); bl >= 1; --bl) {
-      const int64_t b = pair_lds_bytes(P, bl, nullptr);
-      if (b > 0 && b <= std::min(cap, budget)) {
-        spinsum_tile_t t{};
-        t.bl = bl;
-        t.cubes_per_wg = 1;
-        t.variant = SPINSUM_VARIANT_DIRECT_LDS;
-        *tile = t;
-        return SPINSUM_OK;
-      }
-    }
+  const int esz = elem_size(P);
+  auto take = [&](int bl, int64_t cap) {
+    const int64_t b = pair_lds_bytes(P, bl, nullptr);
+    if (b <= 0 || b > std::min(cap, budget)) return false;
+    spinsum_tile_t t{};
+    t.bl = bl;
+    t.cubes_per_wg = 1;
+    t.variant = SPINSUM_VARIANT_DIRECT_LDS;
+    *tile = t;
+    return true;
+  };
+  const int64_t k32 = 32 * 1024, k56 = 56 * 1024;
+  const int top = std::min(P.n, 255);
+  auto row = [&](int bl) { return (int64_t)bl * P.inner * esz; };
+  if (P.n == top && take(P.n, k56)) return SPINSUM_OK;
+  for (int bl = top; bl >= 1; --bl) {
+    const double cover = (double)((P.n + bl - 1) / bl * bl) / P.n;
+    if (P.d > 2 && row(bl) % 64 == 0 && std::pow(cover, P.d) <= 1.5 && take(bl, k32)) return SPINSUM_OK;
   }
+  for (int bl = top - 1; bl >= 1; --bl)
+    if (P.d > 2 && P.n % bl == 0 && row(bl) >= (esz == 8 ? 48 : 32) &&
+        take(bl, !P.inplace && esz == 8 ? k32 : k56))
+      return SPINSUM_OK;
+  for (const int64_t cap : {k32, k56})
+    for (int bl = top; bl >= 1; --bl)
+      if (row(bl) >= 32 && take(bl, cap)) return SPINSUM_OK;
+  for (const int64_t cap : {k32, (int64_t)64 * 1024, budget})
+    for (int bl = top; bl >= 1; --bl)
+      if (take(bl, cap)) return SPINSUM_OK;
   return SPINSUM_ERR_UNSUPPORTED;
 }
 
@@ -1394,13 +1422,25 @@ static spinsum_status apply_pair_tile(spinsum_plan_s* P, const spinsum_tile_t* r
     P->T.nts = choose_nts(*P, P->T, P->pg.norb);
   }
   if (t.threads == 0) {
-    // 512 threads wherever two workgroups fit a CU: each item first builds
-    // its tile list in one wave, and more waves per item issue its loads
-    // sooner afterwards (v=48 o=24, 8^3 tiles: 4.76 against 4.64 TB/s at 256
-    // threads, although waves then limit a CU to 4 workgroups instead of 6)
+    // About three 16-byte chunks per thread, at most 512 threads (1024 where
+    // one workgroup fits a CU).  Whole group cubes are copied a tile at a time,
+    // and small ones are bound by the waves dispatched for them: 4^3 FP64 654
+    // GB/s at 512 threads, 4623 at 64; 8^3 FP64 4600 and, at 256, 5031.  8^3
+    // tiles of 24 KiB items do better with few workgroups in flight, whose
+    // lines the L2 still holds when their other halves are wanted (24^3 FP64
+    // 4.98 ms at 512 threads, 5.38 at 256); 4D items have 256 element orbits
+    // to combine (8^4 FP64 3823 at 256 threads, 3249 at 512)
     const int64_t wg = pair_lds_bytes(*P, P->T.g.bl > 0 ? P->T.g.bl : std::max(1, P->n), nullptr);
     const int64_t per_cu = std::max<int64_t>(1, P->lds_limit / std::max<int64_t>(1, wg));
-    t.threads = per_cu >= 2 ? 512 : 1024;
+    const Geom& g = P->T.g;
+    const int64_t tile_chunks = (int64_t)g.rows * g.bl * g.inner * elem_size(*P) / 16;
+    int64_t chunks = tile_chunks * P->T.max_tiles;
+    if (P->pg.flat) chunks = std::min(chunks, 3 * tile_chunks);  // a tile at a time
+    if (P->pg.flat && P->d <= 3)
+      t.threads = chunks >= 1536 ? 512 : chunks >= 768 ? 256 : chunks >= 384 ? 128 : 64;
+    else
+      t.threads = (P->d == 3 && chunks >= 1536) || (P->d == 2 && chunks >= 768) ? 512 : 256;
+    if (per_cu < 2) t.threads = 1024;
   }
   P->tile = t;
   return SPINSUM_OK;
