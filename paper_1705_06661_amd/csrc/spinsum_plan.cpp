@@ -735,12 +735,26 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
 // parts of one 128-byte line then run far apart), cached stores let the L2
 // merge the partial lines first: 4D o=12 slab +3 %, one 352^3 cube +2.5 %,
 // one 80^4 cube +10 %.
+// Cached also
+//  - out of place where tile rows do not start and end on 64-byte sectors:
+//    the parts of a sector come from different workgroups, nothing has read
+//    it into the L2, and non-temporal parts go to memory one by one (28^3
+//    FP64 2.40 against 4.10 TB/s cached, 36^3 2.41 and 4.05, 46^3 2.12 and
+//    3.54, 150^2 3.98 and 5.03, index pairs of 36^3 2.57 and 3.75; in place,
+//    after the reads, both are equal: 36^3 4.31 and 4.27; whole index-pair
+//    cubes of 34^2, written a cube at a time, 4.36 and 3.89);
+//  - where orbits are packed and rows are part lines: the items of a cube are
+//    few and write neighbouring parts together (32^3 FP32 in place 4.90
+//    against 5.21, out of place 4.68 and 5.29).
 static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits) {
   if (P.flags & SPINSUM_FLAG_NO_NT_STORES) return 0;
   if (P.flags & SPINSUM_FLAG_NT_STORES) return 1;
   const bool whole = (T.g.bl == T.g.n) && !P.pair;
   if (whole) return 1;
   const int64_t row = (int64_t)T.g.bl * T.g.inner * elem_size(P);
+  const int64_t stride = (int64_t)T.g.n * T.g.inner * elem_size(P);
+  if (!P.inplace && T.g.bl < T.g.n && (row % 64 != 0 || stride % 64 != 0)) return 0;
+  if (!P.pair && row < 128 && T.groups.size() < T.orbits.size()) return 0;
   return (row >= 64 && orbits <= 128) ? 1 : 0;
 }
 

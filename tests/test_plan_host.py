@@ -752,3 +752,29 @@ def test_whole_cube_sum_rule():
     assert own((600, 32, 32, 32), 1, 3, cfg3, dtype="f32") == (16, 0)  # packed orbits
     assert own((600, 12, 12, 12, 12), 1, 4, [workloads.antisymmetrizer(4)]) == (6, 0)
     assert own((512, 24, 24, 24), 1, 3, cfg3, flags=ss.SPINSUM_FLAG_NO_XCD_REMAP) == (8, 0)
+
+
+def test_store_mode_of_part_sectors():
+    """Out of place, tile rows that do not start and end on 64-byte sectors
+    take cached stores, in place they keep non-temporal ones; packed orbits of
+    part lines take cached ones either way; the flags override the rule."""
+    cfg3 = [workloads.CONFIG_3D_ALPHA]
+    def nt(n, dtype="f64", inplace=False, flags=0, inner=(), d=3):
+        terms = cfg3 if d == 3 else [[((0, 1), 2.0), ((1, 0), -1.0)]]
+        p = ss.spinsum_plan((8,) + (n,) * d + inner, 1, d, terms, dtype=dtype, inplace=inplace,
+                            flags=HOST | flags)
+        ok, why = ss.spinsum_plan_check_ownership(p)
+        assert ok, why
+        return ss.spinsum_plan_get_info(p)["nt_stores"]
+    assert nt(36) == 0 and nt(36, inplace=True) == 1         # 288-byte strides
+    assert nt(40) == 1 and nt(40, inplace=True) == 1         # 320-byte strides
+    assert nt(150, d=2) == 0 and nt(160, d=2) == 1
+    assert nt(24, inner=(5,)) == 0                           # 160-byte rows
+    assert nt(13) == 1                                       # whole cubes
+    assert nt(32, "f32") == 0 and nt(32, "f32", True) == 0   # packed orbits, 64-byte rows
+    assert nt(36, flags=ss.SPINSUM_FLAG_NT_STORES) == 1
+    assert nt(40, flags=ss.SPINSUM_FLAG_NO_NT_STORES) == 0
+    # (of at most 128 orbits)
+    pair = [ss.spinsum_plan((v,) * d + (n,) * d, d, d, t, flags=HOST | ss.SPINSUM_FLAG_INDEX_PAIRS)
+            for v, n, d, t in ((4, 28, 3, cfg3), (10, 34, 2, [[((0, 1), 2.0), ((1, 0), -1.0)]]))]
+    assert [ss.spinsum_plan_get_info(p)["nt_stores"] for p in pair] == [0, 1]  # tiles, whole cubes
