@@ -619,11 +619,10 @@ extern "C" spinsum_status spinsum_adjoint_coef_grad(spinsum_plan_t P, const void
   }
   // one launch for both where the adjoint is the pre-multiplied operator of
   // the whole group (d <= 3: a 4D orbit's 48 values and 24 sums leave no
-  // registers for the product), but not on the gradient's own tiles where
-  // they are ragged: whole cubes store better (22^3 FP64 957 us in two
-  // launches, 1303 in one)
-  const bool own_ragged = P->cg_pack && !P->cg_split && P->Tc.ragged != 0 && P->T.g.bl >= P->n;
-  if (P->elems != 0 && P->d <= 3 && P->sub == nullptr && !own_ragged &&
+  // registers for the product): 28^3 FP64 1103 us in two launches, 793 in
+  // one; on the gradient's own ragged tiles of 22^3, whole for the adjoint
+  // alone, 957 and 818, of 26^3 1076 and 916
+  if (P->elems != 0 && P->d <= 3 && P->sub == nullptr &&
       !(P->flags & (SPINSUM_FLAG_CHAIN_STAGES | SPINSUM_FLAG_MULTI_PASS)))
     return coef_grad_impl(P, x, g, grad, false, stream, gx);
   st = coef_grad_impl(P, x, g, grad, false, stream);  // (first: gx may be g)

@@ -709,7 +709,7 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
       if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tc) != SPINSUM_OK) continue;
       if (!Tc.fits || (int64_t)Tc.vw * esz != 16 || cg_lds(Tc) > P->lds_limit / 2) continue;
       Tc.nts = choose_nts(*P, Tc, (int64_t)Tc.orbits.size());
-  P->Tc = std::move(Tc);
+      P->Tc = std::move(Tc);
       P->cg_pack = true;
       return;
     }

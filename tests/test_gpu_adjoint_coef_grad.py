@@ -34,7 +34,7 @@ CASES = [
     ((2, 32, 32, 32), 3, F64, True, 0),        # tiles, one tensor in LDS
     ((2, 36, 36, 36), 3, F64, False, 0),       # ragged tiles
     ((2, 24, 24, 24), 3, F64, False, 0),       # the gradient's own tiles
-    ((2, 22, 22, 22), 3, F64, False, 0),       # ragged ones: two launches
+    ((2, 22, 22, 22), 3, F64, False, 0),       # ragged ones
     ((2, 32, 32, 32), 3, F32, False, 0),       # two tensors in LDS, packed orbits
     ((2, 16, 16, 16, 8), 3, F64, False, 0),    # inner runs
     ((3, 33, 33), 2, F64, False, 0),
