@@ -122,7 +122,7 @@ LaunchCfg exec_cfg(const spinsum_plan_s* P, bool chain) {
     return c;
   }
   if (P->x_own) {
-    c.kind = kVariantAnyRows;
+    c.kind = Tl.any_rows ? kVariantAnyRows : SPINSUM_VARIANT_DIRECT_LDS;
     c.k = pick_kernel<T>(P->d, c.kind, Tl.vw, chain, Tl.nts != 0, 0);
     c.shmem = ((size_t)Tl.lds_elems * sizeof(T) + 15) / 16 * 16 + (size_t)Tl.max_rep_cnt * 4;
     c.threads = P->x_threads;

@@ -66,3 +66,25 @@ def test_store_modes(case):
     want = oracle.spinsum(xh, terms, gf, d, nthreads=8)
     have = outs[0][0].cpu().to(F64).numpy()
     assert np.linalg.norm(have - want) <= TOL[dtype] * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n,dtype", [(30, F64), (38, F64), (46, F64), (36, F32), (44, F32)])
+def test_wide_tiles(n, dtype):
+    """The wider tiles of the sum, bitwise against explicit 8^3 ones, forward
+    and adjoint, out of place and in place."""
+    shape = (3, n, n, n)
+    terms = [(p, 0.5 + 0.25 * i) for i, p in enumerate(itertools.permutations(range(3)))]
+    x = workloads.uniform(shape, 9100 + n, device=DEV, dtype=dtype)
+    for inplace in (False, True):
+        p = ss.spinsum_plan(shape, 1, 3, [terms], dtype=dtype, inplace=inplace)
+        q = ss.spinsum_plan(shape, 1, 3, [terms], dtype=dtype, inplace=inplace)
+        ss.spinsum_plan_set_tile(q, 8, variant=ss.SPINSUM_VARIANT_DIRECT_LDS)
+        assert ss.spinsum_plan_get_info(p)["sum_bl"] > 8
+        assert ss.spinsum_plan_get_info(q)["sum_bl"] == 0
+        for run in (ss.spinsum_exec, ss.spinsum_adjoint):
+            outs = []
+            for plan in (p, q):
+                y = x.clone() if inplace else torch.full_like(x, float("nan"))
+                run(plan, y if inplace else x, y)
+                outs.append(y)
+            assert torch.equal(*outs)

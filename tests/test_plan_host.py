@@ -778,3 +778,19 @@ def test_store_mode_of_part_sectors():
     pair = [ss.spinsum_plan((v,) * d + (n,) * d, d, d, t, flags=HOST | ss.SPINSUM_FLAG_INDEX_PAIRS)
             for v, n, d, t in ((4, 28, 3, cfg3), (10, 34, 2, [[((0, 1), 2.0), ((1, 0), -1.0)]]))]
     assert [ss.spinsum_plan_get_info(p)["nt_stores"] for p in pair] == [0, 1]  # tiles, whole cubes
+
+
+@pytest.mark.parametrize("n,dtype,sum_bl", [
+    (30, "f64", 10), (34, "f64", 0), (36, "f64", 0), (40, "f64", 0), (46, "f64", 10),
+    (54, "f64", 10), (36, "f32", 12), (40, "f32", 0), (48, "f32", 0), (52, "f32", 0),
+    (60, "f32", 12)])
+def test_wide_tile_rule(n, dtype, sum_bl):
+    """The sum takes wider tiles where 8^3 rows lie off 32-byte boundaries and
+    the wider ones cover at most 8/7 of the extent; the replay covers them."""
+    for inplace in (False, True):
+        p = ss.spinsum_plan((2, n, n, n), 1, 3, [workloads.CONFIG_3D_ALPHA], dtype=dtype,
+                            inplace=inplace, flags=HOST)
+        i = ss.spinsum_plan_get_info(p)
+        assert (i["bl"], i["sum_bl"]) == (8, sum_bl)
+        ok, why = ss.spinsum_plan_check_ownership(p)
+        assert ok, why
