@@ -29,13 +29,18 @@
 //   k_rows    one item per workgroup, tile rows that start on any element
 //             (extents whose rows are not whole 16-byte chunks), loads
 //             straight into LDS but for the ends of the rows;
+//   k_cube    persistent, whole cubes of which one fits a CU, the next one
+//             in registers;
 //   k_exec    one item per workgroup, loads through registers into padded
 //             LDS (by request);
 //   k_pipe    persistent, next item prefetched into registers;
 //   k_batched many tensors, one item of the cost-sorted list per workgroup;
 //   k_pair    index-pair form: one tile orbit of combined (partner, group)
 //             blocks per workgroup, its tile list built in the workgroup;
-//   k_cgrad   coefficient gradient (x and the upstream gradient in LDS).
+//   k_cgrad, k_cgrad_split   coefficient gradient, alone or with the
+//             adjoint (both tensors, or one, in LDS);
+//   k_unpack_gather   unpacking, every element formed where it is stored
+//             from packed values in LDS.
 // One-shot grids are XCD-grouped: the workgroups of XCD x (blockIdx % 8 == x)
 // take a contiguous range of items, so the tile orbits of one cube -- which
 // share cache lines along the fastest axis -- meet in the same L2.  The work
