@@ -1286,7 +1286,11 @@ static spinsum_status choose_pair_tile(const spinsum_plan_s& P, spinsum_tile_t* 
   const int64_t k32 = 32 * 1024, k56 = 56 * 1024;
   const int top = std::min(P.n, 255);
   auto row = [&](int bl) { return (int64_t)bl * P.inner * esz; };
-  if (P.n == top && take(P.n, k56)) return SPINSUM_OK;
+  // (whole cubes of more than 32 KiB, but not where they leave half of the
+  // CUs idle: 10^3 FP64, 84 items, 9.4 us whole and 8.3 in 8^3 tiles, 165
+  // items 9.9 and 12.0; 12^3 FP32, 35 items, 9.3 and 6.8)
+  const bool few = P.d == 3 && multiset_count(P.pv, P.d) * P.ncubes < P.num_cus / 2;
+  if (P.n == top && take(P.n, few ? k32 : k56)) return SPINSUM_OK;
   for (int bl = top; bl >= 1; --bl) {
     const double cover = (double)((P.n + bl - 1) / bl * bl) / P.n;
     if (P.d > 2 && row(bl) % 64 == 0 && std::pow(cover, P.d) <= 1.5 && take(bl, k32)) return SPINSUM_OK;
@@ -1495,6 +1499,11 @@ static spinsum_status apply_pair_tile(spinsum_plan_s* P, const spinsum_tile_t* r
       t.threads = chunks >= 1536 ? 512 : chunks >= 768 ? 256 : chunks >= 384 ? 128 : 64;
     else
       t.threads = (P->d == 3 && chunks >= 1536) || (P->d == 2 && chunks >= 768) ? 512 : 256;
+    // (fewer items than CUs: no wave waits to be dispatched, an item's own
+    // time counts: 10^3 FP32, 84 items, 10.6 us at 128 threads, 8.7 at 512;
+    // 6^3 FP64, 165 items, 9.1 and 8.0; not for tiles of less than a wave's
+    // chunks: 4^3 FP64 7.2 and 7.8)
+    if (P->pg.flat && P->d <= 3 && P->T.nitems < P->num_cus && tile_chunks >= 64) t.threads = 512;
     if (per_cu < 2) t.threads = 1024;
   }
   P->tile = t;

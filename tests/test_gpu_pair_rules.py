@@ -26,12 +26,12 @@ CASES = [
     # V, N, d, dtype, inplace, bl, threads
     (9, 4, 3, F64, True, 4, 64),
     (8, 5, 3, F32, False, 5, 64),
-    (6, 7, 3, F64, True, 7, 128),
-    (6, 8, 3, F32, False, 8, 128),
-    (5, 9, 3, F64, True, 9, 256),
-    (4, 10, 3, F64, False, 10, 256),
+    (11, 7, 3, F64, True, 7, 128),
+    (11, 8, 3, F32, False, 8, 128),
+    (11, 9, 3, F64, True, 9, 256),
+    (11, 10, 3, F64, False, 10, 256),
     (4, 12, 3, F64, True, 6, 256),
-    (4, 12, 3, F32, True, 12, 256),
+    (11, 12, 3, F32, True, 12, 256),
     (3, 20, 3, F64, True, 10, 512),
     (3, 20, 3, F64, False, 8, 512),    # ragged
     (3, 20, 3, F32, True, 8, 256),
@@ -39,9 +39,15 @@ CASES = [
     (3, 6, 4, F64, True, 4, 256),
     (4, 4, 4, F64, False, 4, 256),
     (12, 8, 2, F64, True, 8, 64),
-    (9, 21, 2, F64, False, 21, 128),
+    (23, 21, 2, F64, False, 21, 128),
     (5, 48, 2, F64, True, 48, 512),
     (3, 100, 2, F64, True, 40, 512),
+    # fewer items than CUs
+    (6, 7, 3, F64, True, 7, 512),
+    (4, 10, 3, F64, False, 8, 512),
+    (7, 10, 3, F32, True, 10, 512),
+    (4, 12, 3, F32, True, 8, 256),
+    (9, 21, 2, F64, False, 21, 512),
 ]
 
 
