@@ -717,8 +717,8 @@ def test_lds_pipeline_variant_needs_two_buffers():
 ])
 def test_rows_tiling_rule(shape, gf, d, dtype, sum_bl):
     """Where the planner's tile has no rows of whole 16-byte chunks, exec runs
-    on tiles of their own whose rows start on any element; the checker
-    replays both tilings."""
+    on tiles of their own whose rows start on any element; the ownership
+    replay covers both tilings."""
     terms = [[(p, 1.0) for p in itertools.permutations(range(d))]]
     p = ss.spinsum_plan(shape, gf, d, terms, dtype=dtype, flags=HOST)
     assert ss.spinsum_plan_get_info(p)["sum_bl"] == sum_bl
