@@ -190,7 +190,7 @@ struct CGradArgs {
   T* gx;                   // ADJ: the adjoint applied to gr
   const T* coef;           // ADJ: the adjoint's coefficient vector
   int32_t nts;             // ADJ: non-temporal stores
-  int32_t pad;
+  int32_t red_off;         // LDS bytes of the waves' sums, where nothing is live by then
 };
 
 template <typename T>
@@ -2090,8 +2090,10 @@ __global__ void __launch_bounds__(D <= 3 ? 2 * kThreads : kThreads) k_cgrad(cons
       redo_item<T, D, false, true>(g, od, reps, as_const(a.coef), 1, ncub, a.gr + cube0 * g.cube_elems, U);
   }
   // workgroup sum: within each wave, then across the waves through LDS
+  // (red_off: x's tiles, which are done with, or behind everything where
+  // these are smaller than the sums: the adjoint's tiles follow them)
   __syncthreads();  // every wave is done with the tiles
-  double* red = reinterpret_cast<double*>(smem);
+  double* red = reinterpret_cast<double*>(smem + a.red_off);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int p = 0; p < DF; ++p) {
@@ -2261,7 +2263,7 @@ __global__ void __launch_bounds__(kThreads, 6) k_cgrad_split(const CGradArgs<T> 
   } else {
     __syncthreads();
   }
-  double* red = reinterpret_cast<double*>(ADJ ? rep_lds : smem);
+  double* red = reinterpret_cast<double*>(smem + a.red_off);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int p = 0; p < DF; ++p) {

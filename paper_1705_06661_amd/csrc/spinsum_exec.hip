@@ -482,8 +482,7 @@ spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, voi
   a.nitems = Tl.nitems;
   a.lds_tile_bytes = (int32_t)(((size_t)Tl.lds_elems * sizeof(T) + 15) / 16 * 16);
   const int df = P->G.df;
-  // LDS: x tiles | gradient tiles (k_cgrad only) | representative lists;
-  // the partial sums of the waves reuse it at the end
+  // LDS: x tiles | gradient tiles (k_cgrad only) | representative lists
   const bool adj = gx != nullptr;
   const size_t lds = (split ? 1 : 2) * (size_t)a.lds_tile_bytes + (size_t)Tl.max_rep_cnt * 4;
   // whole cubes of which a CU holds one pair: 512 threads (both gradients of
@@ -492,15 +491,24 @@ spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, voi
   // better (16^3 FP32 315 against 405 us)
   const bool wide = P->d <= 3 && !split && Tl.g.bl == Tl.g.n && 2 * (int64_t)lds > P->lds_limit;
   const int threads = wide ? 2 * kThreads : kThreads;
+  // the waves' sums take the place of tiles that are done with: x's, and
+  // with the adjoint, whose tiles are stored meanwhile, the representative
+  // list's (one tensor in LDS) or, where x's tiles are smaller than the sums
+  // (groups of 1 to 3), the bytes behind the lists
   const size_t red = (size_t)(threads / 64) * df * sizeof(double);
-  size_t shmem = std::max(lds, red);
+  size_t red_off = 0;
+  if (adj && split)
+    red_off = (size_t)a.lds_tile_bytes;
+  else if (adj && (size_t)a.lds_tile_bytes < red)
+    red_off = (lds + 7) / 8 * 8;
+  a.red_off = (int32_t)red_off;
+  const size_t shmem = std::max(lds, red_off + red);
   if (adj) {
     a.gx = reinterpret_cast<T*>(gx);
     const CoefSel sel = coef_sel(P, true);
     a.coef = reinterpret_cast<const T*>(P->d_mats) + sel.offset;
     a.sparse = sel.sparse;
     a.nts = Tl.nts;
-    if (split) shmem = (size_t)a.lds_tile_bytes + std::max<size_t>((size_t)Tl.max_rep_cnt * 4, red);
   }
   if ((int64_t)shmem > P->lds_limit) return SPINSUM_ERR_UNSUPPORTED;
   const void* k = pick_cgrad<T>(P->d, split, adj);
