@@ -400,7 +400,10 @@ void spinsum_graph_destroy(spinsum_graph_t graph);
 /* Time candidate tile configurations of a single-tensor plan on the given
  * buffers (their contents are overwritten with unspecified values), keep
  * the fastest in the plan and, if cache_path is not NULL, record it in that
- * cache file (one "key value" line per configuration).  *best_ms receives
+ * cache file (one "key value" line per configuration).  The planner's own
+ * choice is a candidate where it runs on tiles that no request names
+ * (spinsum_plan_info_t.sum_bl); where it wins, best->bl is 0, which
+ * spinsum_plan_set_tile and the cache file take for that choice.  *best_ms receives
  * the best time of one exec.  Synchronises the stream.  Index-pair plans:
  * SPINSUM_ERR_UNSUPPORTED.  Batched plans: in/out are the DEVICE arrays of
  * block pointers of spinsum_exec_batched; the candidates are the size up to

@@ -1510,7 +1510,8 @@ static spinsum_status apply_pair_tile(spinsum_plan_s* P, const spinsum_tile_t* r
   return SPINSUM_OK;
 }
 
-static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req) {
+static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req,
+                                 bool use_cache = true) {
   if (P->pair) return apply_pair_tile(P, req);
   spinsum_tile_t t{};
   bool chosen = false;  // tile picked by the planner (not requested, not cached)
@@ -1520,7 +1521,7 @@ static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req) {
     if (t.threads < 0) t.threads = 0;
     if (t.cubes_per_wg <= 0) t.cubes_per_wg = 1;
   } else if (P->n > 0 && P->ncubes > 0) {
-    if (!cache_lookup(*P, &t)) {
+    if (!use_cache || !cache_lookup(*P, &t)) {
       spinsum_status st = choose_tile(*P, P->n, P->ncubes, vmax, &t, true);
       if (st != SPINSUM_OK) return st;
       chosen = true;
@@ -1586,6 +1587,7 @@ static spinsum_status apply_tile(spinsum_plan_s* P, const spinsum_tile_t* req) {
   P->tile = t;
   P->T = std::move(T);
   P->x_own = false;
+  P->chosen = chosen;
   if (chosen) {
     choose_rows_tiling(P);
     choose_cube_tiling(P);
@@ -1950,10 +1952,8 @@ extern "C" spinsum_status spinsum_plan_batched(spinsum_plan_t* plan, int nblocks
   return SPINSUM_OK;
 }
 
-extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_tile_t* tile) {
-  if (P == nullptr || tile == nullptr || P->batched) return SPINSUM_ERR_INVALID_ARG;
-  if (P->sub) return spinsum_plan_set_tile(P->sub, tile);
-  if (tile->bl < 0 || tile->cubes_per_wg < 0) return SPINSUM_ERR_INVALID_ARG;
+namespace spinsum {
+spinsum_status retile(spinsum_plan_s* P, const spinsum_tile_t* tile, bool use_cache) {
   spinsum_tile_t keep = P->tile;
   Tiling keepT = P->T;
   const PairGeom keep_pg = P->pg;
@@ -1961,7 +1961,8 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
   const Tiling keep_tx = P->Tx;
   const bool keep_own = P->x_own;
   const int keep_x_threads = P->x_threads;
-  spinsum_status st = apply_tile(P, tile);
+  const bool keep_chosen = P->chosen;
+  spinsum_status st = apply_tile(P, tile, use_cache);
   if (st == SPINSUM_OK) st = upload_tables(P);
   if (st != SPINSUM_OK) {
     P->tile = keep;
@@ -1971,10 +1972,19 @@ extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_
     P->Tx = keep_tx;
     P->x_own = keep_own;
     P->x_threads = keep_x_threads;
+    P->chosen = keep_chosen;
     spinsum_status st2 = upload_tables(P);
     (void)st2;
   }
   return st;
+}
+}  // namespace spinsum
+
+extern "C" spinsum_status spinsum_plan_set_tile(spinsum_plan_t P, const spinsum_tile_t* tile) {
+  if (P == nullptr || tile == nullptr || P->batched) return SPINSUM_ERR_INVALID_ARG;
+  if (P->sub) return spinsum_plan_set_tile(P->sub, tile);
+  if (tile->bl < 0 || tile->cubes_per_wg < 0) return SPINSUM_ERR_INVALID_ARG;
+  return retile(P, tile, true);
 }
 
 extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_info_t* info) {

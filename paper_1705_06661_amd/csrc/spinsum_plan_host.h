@@ -106,6 +106,7 @@ struct spinsum_plan_s {
   spinsum::Tiling Tx;
   bool x_own = false;
   int x_threads = 256;
+  bool chosen = false;  // tile: picked by the planner (not requested, not cached)
   // unpacking's own tiling where it differs from T (pk_own): the largest
   // items that fit a CU (see build_unpack_tiling), with their workgroup size
   spinsum::Tiling Tu;
@@ -190,6 +191,9 @@ spinsum_status choose_tile(const spinsum_plan_s& P, int n, int64_t ncubes, int v
                            spinsum_tile_t* tile, bool single);
 int max_vector_width(const spinsum_plan_s& P, int64_t row);
 spinsum_status upload_tables(spinsum_plan_s* P);
+// spinsum_plan_set_tile of a group plan; use_cache: a tile edge of 0 may be
+// answered from the autotuner's cache file
+spinsum_status retile(spinsum_plan_s* P, const spinsum_tile_t* tile, bool use_cache);
 
 spinsum_status build_batched(spinsum_plan_s* P, int64_t item_bytes);
 void free_device(spinsum_plan_s* P);

@@ -8,6 +8,7 @@
 //
 // Cache file: plain text, one line per configuration:
 //   <key> <bl> <cubes_per_wg> <threads> <lds_pad> <variant> <item_tiles> <ms>
+// (bl = 0: the planner's own choice was the fastest).
 // key = d<d>_n<N>_r<inner run>_<f64|f32>_ip<0|1>_c<floor(log2(ncubes))>_<arch>.
 // Batched plans: <key> <whole-cube item KiB> <persistent 0|1> <ms>, with
 // key = batch_b<blocks>_e<elements>_d<d>_<f64|f32>_ip<0|1>_<arch>.
@@ -122,10 +123,10 @@ bool cache_lookup(const spinsum_plan_s& P, spinsum_tile_t* tile) {
     if (!(is >> k >> t.bl >> t.cubes_per_wg >> t.threads >> t.lds_pad >> t.variant >> t.item_tiles >> ms))
       continue;
     if (k != key) continue;
-    if (t.bl < 1 || t.bl > P.n || t.cubes_per_wg < 1) continue;
+    if (t.bl < 0 || t.bl > P.n || t.cubes_per_wg < 1) continue;
     if (t.variant < 0 || t.variant > SPINSUM_VARIANT_LDS_PIPELINE) continue;
-    *tile = t;  // the last matching line wins
-    found = true;
+    found = t.bl > 0;  // the last matching line wins
+    if (found) *tile = t;
   }
   return found;
 }
@@ -222,7 +223,21 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
   const int n = P->n, d = P->d;
   int64_t cube_bytes = (int64_t)esz * P->inner;
   for (int m = 0; m < d; ++m) cube_bytes *= n;
-  // candidates: kernel variant x tile edge (x cubes per workgroup)
+  hipEvent_t e0, e1;
+  if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
+    (void)hipGetLastError();
+    return SPINSUM_ERR_HIP;
+  }
+  // the tile to go back to where nothing can be timed (every set_tile below
+  // replaces it; a tile edge of 0 stands for the planner's own choice)
+  const spinsum_tile_t choose{0, 1, 0, 0, 0, 0};
+  const spinsum_tile_t keep = P->chosen ? choose : P->tile;
+  // candidates: kernel variant x tile edge (x cubes per workgroup); first the
+  // planner's own choice where it runs on tiles that no request names
+  // (spinsum_plan_info_t.sum_bl), asked for before any other tile is set and
+  // not answered from a cache file
+  std::vector<spinsum_tile_t> cands;
+  if (retile(P, &choose, false) == SPINSUM_OK && P->x_own) cands.push_back(choose);
   std::vector<spinsum_tile_t> shapes;
   for (int cpw = 1; cpw <= 64; cpw *= 2) {
     if (cpw * cube_bytes + 1024 > P->lds_limit || cpw > P->ncubes) break;
@@ -240,10 +255,6 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
     shapes.push_back({bl, 1, 256, 0, 0, mo});
     if (2 * mo <= kMaxGroupTiles) shapes.push_back({bl, 1, 256, 0, 0, 2 * mo});
   }
-  std::vector<spinsum_tile_t> cands;
-  // the planner's own choice first: where it runs on tiles that no request
-  // names (spinsum_plan_info_t.sum_bl), winning keeps it
-  if (P->x_own) cands.push_back(spinsum_tile_t{0, 1, 0, 1, 0, 0});
   for (const spinsum_tile_t& sh : shapes) {
     spinsum_tile_t t = sh;
     t.lds_pad = 0;
@@ -263,17 +274,11 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
       cands.push_back(t);
     }
   }
-  spinsum_tile_t keep = P->tile;
   spinsum_tile_t win{};
   float win_ms = 0;
   bool have = false;
-  hipEvent_t e0, e1;
-  if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
-    (void)hipGetLastError();
-    return SPINSUM_ERR_HIP;
-  }
   for (const spinsum_tile_t& t : cands) {
-    if (spinsum_plan_set_tile(P, &t) != SPINSUM_OK) continue;
+    if (retile(P, &t, false) != SPINSUM_OK) continue;
     if (spinsum_exec(P, in, out, stream) != SPINSUM_OK) continue;  // warm-up
     const int reps = 3;
     float ms_min = 1e30f;
@@ -296,11 +301,11 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  spinsum_status st = spinsum_plan_set_tile(P, have ? &win : &keep);
+  spinsum_status st = retile(P, have ? &win : &keep, false);
   if (st != SPINSUM_OK) return st;
-  if (best) *best = P->tile;
+  const spinsum_tile_t result = have ? win : P->tile;
+  if (best) *best = result;
   if (best_ms) *best_ms = have ? win_ms : 0.0f;
-  // (the planner's own choice needs no record)
-  if (have && win.bl > 0 && cache_path != nullptr && *cache_path) cache_store(*P, cache_path, P->tile, win_ms);
+  if (have && cache_path != nullptr && *cache_path) cache_store(*P, cache_path, result, win_ms);
   return have ? SPINSUM_OK : SPINSUM_ERR_UNSUPPORTED;
 }
