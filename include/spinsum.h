@@ -166,7 +166,10 @@ typedef struct {
   int exec_group_first;  /* its first dim */
   int persistent_per_cu; /* persistent kernel variants and persistent batched plans:
                             workgroups launched per CU (the kernel's occupancy, taken
-                            when the tables are built); else 0 */
+                            when the tables are built); 1 also where exec and adjoint run
+                            whole cubes of a tile that the planner chose persistently, one
+                            workgroup of 1024 threads per CU (one cube fits a CU, at least
+                            two cubes per CU, d <= 3); else 0 */
   int nt_loads;          /* 1: the direct-LDS kernel loads tiles with the non-temporal
                             policy, chosen where every work item owns the 128-byte lines
                             it reads (whole cubes, or tile rows that start and end on line
@@ -401,9 +404,10 @@ void spinsum_graph_destroy(spinsum_graph_t graph);
  * buffers (their contents are overwritten with unspecified values), keep
  * the fastest in the plan and, if cache_path is not NULL, record it in that
  * cache file (one "key value" line per configuration).  The planner's own
- * choice is a candidate where it runs on tiles that no request names
- * (spinsum_plan_info_t.sum_bl); where it wins, best->bl is 0, which
- * spinsum_plan_set_tile and the cache file take for that choice.  *best_ms receives
+ * choice is a candidate where no request names its tiles or its kernel
+ * (spinsum_plan_info_t.sum_bl, persistent_per_cu); where it wins, best->bl
+ * is 0, which spinsum_plan_set_tile and the cache file take for that choice.
+ * *best_ms receives
  * the best time of one exec.  Synchronises the stream.  Index-pair plans:
  * SPINSUM_ERR_UNSUPPORTED.  Batched plans: in/out are the DEVICE arrays of
  * block pointers of spinsum_exec_batched; the candidates are the size up to

@@ -497,7 +497,7 @@ def spinsum_graph_destroy(graph: Graph):
 
 def spinsum_autotune(plan: Plan, inp, out, stream=None, cache_path: Optional[str] = None):
     """Time tile candidates on these buffers (overwritten) and keep the best
-    (bl 0: the planner's own choice, on tiles that no request names).
+    (bl 0: the planner's own choice, where no request names it).
     Batched plans take one tensor per block in `inp` and `out` (lists) and
     tune the whole-cube item size and the persistent launch; the result's
     cubes_per_wg is the item size in KiB and variant 1 the persistent

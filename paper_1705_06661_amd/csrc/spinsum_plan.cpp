@@ -919,8 +919,10 @@ static void choose_unpack_gather(spinsum_plan_s* P) {
 // Whole cubes of which one fits a CU, at least two per workgroup: k_cube.
 // (Two or more cubes to a CU hide each other's combine step already: 20^3
 // FP64 6.08 TB/s with k_lds, 5.94 with k_cube; 24^3 FP32 6.00 and 5.26.)
+// Only where the planner chose the tile: a requested one names its workgroup
+// size and runs one item per workgroup.
 bool cube_persistent(const spinsum_plan_s& P, const Tiling& T) {
-  if (P.pair || P.batched || P.d > 3 || P.n <= 0 || T.g.bl != P.n || T.g.cpw != 1 ||
+  if (!P.chosen || P.pair || P.batched || P.d > 3 || P.n <= 0 || T.g.bl != P.n || T.g.cpw != 1 ||
       P.tile.variant != SPINSUM_VARIANT_DIRECT_LDS || P.ncubes < 2 * (int64_t)P.num_cus)
     return false;
   if (!T.nts || !T.ntl || (P.flags & (SPINSUM_FLAG_NO_XCD_REMAP | SPINSUM_FLAG_REVERSE_ORDER)))
@@ -2017,6 +2019,7 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
       (!P->batched && !P->pair &&
        ((v == SPINSUM_VARIANT_REG_PIPELINE && P->T.nts) || v == SPINSUM_VARIANT_LDS_PIPELINE)))
     info->persistent_per_cu = P->occ_blocks;
+  if (cube_persistent(*P, P->x_own ? P->Tx : P->T)) info->persistent_per_cu = 1;
   info->d = P->d;
   info->n = P->n;
   info->ncubes = P->ncubes;

@@ -233,11 +233,12 @@ extern "C" spinsum_status spinsum_autotune(spinsum_plan_t P, void* in, void* out
   const spinsum_tile_t choose{0, 1, 0, 0, 0, 0};
   const spinsum_tile_t keep = P->chosen ? choose : P->tile;
   // candidates: kernel variant x tile edge (x cubes per workgroup); first the
-  // planner's own choice where it runs on tiles that no request names
-  // (spinsum_plan_info_t.sum_bl), asked for before any other tile is set and
-  // not answered from a cache file
+  // planner's own choice where no request names its tiles or its kernel
+  // (spinsum_plan_info_t.sum_bl, k_cube), asked for before any other tile is
+  // set and not answered from a cache file
   std::vector<spinsum_tile_t> cands;
-  if (retile(P, &choose, false) == SPINSUM_OK && P->x_own) cands.push_back(choose);
+  if (retile(P, &choose, false) == SPINSUM_OK && (P->x_own || cube_persistent(*P, P->T)))
+    cands.push_back(choose);
   std::vector<spinsum_tile_t> shapes;
   for (int cpw = 1; cpw <= 64; cpw *= 2) {
     if (cpw * cube_bytes + 1024 > P->lds_limit || cpw > P->ncubes) break;

@@ -156,6 +156,7 @@ int main(int, char** argv) {
       {"rows_f32", {64, 39, 39, 39}, 3, SPINSUM_F32, 0},
       {"wide_f64", {64, 30, 30, 30}, 3, SPINSUM_F64, 1},   // wide tiles
       {"cube_f64", {512, 24, 24, 24}, 3, SPINSUM_F64, 1},  // whole cubes in place of tiles
+      {"cube_oop", {512, 24, 24, 24}, 3, SPINSUM_F64, 0},  // the planner's whole cubes, persistent
   };
   for (const Shape& s : shapes) run_case(s, argv[1]);
   std::printf(g_failed ? "%d checks FAILED\n" : "PASSED\n", g_failed);

@@ -40,4 +40,4 @@ def test_autotune_keeps_the_planners_choice(tmp_path):
     env = {k: v for k, v in os.environ.items() if k != "SPINSUM_AUTOTUNE_CACHE"}
     r = subprocess.run([exe, str(tmp_path)], env=env, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "PASSED" in r.stdout, r.stdout + r.stderr
-    assert r.stdout.count("ok ") == 4
+    assert r.stdout.count("ok ") == 5
