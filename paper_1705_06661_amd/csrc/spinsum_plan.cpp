@@ -869,9 +869,11 @@ int64_t gather_lds_bytes(const spinsum_plan_s& P, int64_t cpi, int64_t ncomb, in
 //    28^3 FP32 6.39 against 4.9, 16^3 x 3 6.80 against 6.15; not for edges
 //    of whole LDS rows (32^3 FP32 4.57 against 5.0);
 //  - too few cubes to fill the CUs (ten 48^3 cubes: 7.7 against 13.2 us), or
-//    small ones of less than 64 MiB in all (600 16^3 cubes: 9.9 against 11.1).
+//    small ones of less than 64 MiB in all (600 16^3 cubes: 9.9 against 11.1);
+//  - SPINSUM_FLAG_NO_NT_STORES: the gather always stores non-temporally.
 static void choose_unpack_gather(spinsum_plan_s* P) {
   P->pk_gather = false;
+  if (P->flags & SPINSUM_FLAG_NO_NT_STORES) return;
   if (P->pair || P->batched || P->ncubes <= 0 || P->elems <= 0) return;
   const int d = P->d, n = P->n, esz = elem_size(*P);
   if (n < d || n > (d == 4 ? 255 : 1023)) return;
