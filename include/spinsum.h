@@ -116,7 +116,8 @@ typedef struct spinsum_graph_s* spinsum_graph_t;
  *     cubes.  cubes_per_wg: whole-cube mode only, spectator cubes per
  *     workgroup (>= 1).  threads: workgroup size, 256, 512 or 1024 for
  *     SPINSUM_VARIANT_DIRECT_LDS (0: chosen so that the workgroups that fit
- *     a CU's LDS hold about 16 waves), always 256 for the other variants.
+ *     a CU's LDS hold about 16 waves), always 256 for the other variants;
+ *     index pairs in whole group cubes (bl == N, d <= 3) also 64 or 128.
  *     lds_pad: 1 = odd LDS strides (register variants only).  variant:
  *     SPINSUM_VARIANT_*.  0 in bl / cubes_per_wg / threads / variant means
  *     "choose". */

@@ -1470,7 +1470,9 @@ static spinsum_status apply_pair_tile(spinsum_plan_s* P, const spinsum_tile_t* r
   } else {
     t.bl = std::max(1, P->n);
   }
-  if (t.threads != 0 && t.threads != 256 && t.threads != 512 && t.threads != 1024)
+  // (64 and 128: the sizes the rule below takes for small whole group cubes)
+  const bool small = t.threads == 64 || t.threads == 128;
+  if (t.threads != 0 && !small && t.threads != 256 && t.threads != 512 && t.threads != 1024)
     return SPINSUM_ERR_UNSUPPORTED;
   if (t.variant != SPINSUM_VARIANT_AUTO && t.variant != SPINSUM_VARIANT_DIRECT_LDS)
     return SPINSUM_ERR_UNSUPPORTED;
@@ -1484,6 +1486,7 @@ static spinsum_status apply_pair_tile(spinsum_plan_s* P, const spinsum_tile_t* r
     if (st != SPINSUM_OK) return st;
     P->T.nts = choose_nts(*P, P->T, P->pg.norb);
   }
+  if (small && !(P->elems > 0 && P->pg.flat && P->d <= 3)) return SPINSUM_ERR_UNSUPPORTED;
   if (t.threads == 0) {
     // About three 16-byte chunks per thread, at most 512 threads (1024 where
     // one workgroup fits a CU).  Whole group cubes are copied a tile at a time,
