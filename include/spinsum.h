@@ -181,7 +181,9 @@ typedef struct {
                             several items share in the L2 */
   int coef_grad_split;   /* 1: spinsum_coef_grad keeps one tensor in LDS at a time (the
                             upstream gradient waits in registers while x's orbits are
-                            gathered), on this plan's tiling; 0: both tensors in LDS */
+                            gathered), on this plan's tiling or, where its whole cubes
+                            are too large for both tensors, on tiles of the gradient's
+                            own; 0: both tensors in LDS */
   int unpack_bl;         /* tile edge of spinsum_unpack: its own tiling of the largest
                             items a CU holds (whole cubes where a cube fits the LDS, else
                             the largest edge whose rows are whole 128-byte lines), or the

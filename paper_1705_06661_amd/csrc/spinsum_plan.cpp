@@ -1067,6 +1067,7 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
   P->cg_own_split = false;
   choose_unpack_tiling(P);
   choose_unpack_gather(P);
+  if (!P->pair && !P->batched) build_cgrad_tiling(P);
   if (P->flags & SPINSUM_FLAG_HOST_ONLY) return SPINSUM_OK;
   Uploads U;
   // coefficient vectors in the storage type: forward | adjoint | stages | adjoint stages
@@ -1097,7 +1098,6 @@ spinsum_status upload_tables(spinsum_plan_s* P) {
       U.add(&P->d_x_orbits, P->Tx.groups.data(), P->Tx.groups.size());
       U.add(&P->d_x_reps, P->Tx.reps.data(), P->Tx.reps.size());
     }
-    build_cgrad_tiling(P);
     if (P->cg_pack) {
       U.add(&P->d_cg_orbits, P->Tc.groups.data(), P->Tc.groups.size());
       U.add(&P->d_cg_reps, P->Tc.reps.data(), P->Tc.reps.size());
@@ -2006,7 +2006,7 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
     for (double v : P->expanded) nz += (v != 0.0);
     info->nterms_expanded = nz;
     info->exec_group_first = P->sub_first;
-    info->coef_grad_split = P->cg_split ? 1 : 0;  // the gradient runs on the whole group
+    info->coef_grad_split = (P->cg_split || P->cg_own_split) ? 1 : 0;  // the gradient runs on the whole group
     info->unpack_bl = P->pk_own ? P->Tu.g.bl : P->T.g.bl;  // and so does unpacking
     info->unpack_persistent =
         (P->pk_own && P->pk_persist && !(P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 1 : 0;
@@ -2041,7 +2041,7 @@ extern "C" spinsum_status spinsum_plan_get_info(spinsum_plan_t P, spinsum_plan_i
   info->pair_extent = P->pair ? P->pv : 0;
   info->nt_stores = P->batched ? 1 : P->T.nts;
   info->nt_loads = P->batched ? 1 : P->T.ntl;
-  info->coef_grad_split = P->cg_split ? 1 : 0;
+  info->coef_grad_split = (P->cg_split || P->cg_own_split) ? 1 : 0;
   info->unpack_bl = (P->batched || P->pair) ? 0 : P->pk_own ? P->Tu.g.bl : P->T.g.bl;
   info->unpack_nt_stores =
       (!P->batched && !P->pair && (P->pk_own ? P->Tu.nts : P->T.nts) != 0) ? 1 : 0;
@@ -2452,8 +2452,13 @@ extern "C" spinsum_status spinsum_plan_check_ownership(spinsum_plan_t P, int blo
     const std::string bad_rows = check_tiling(*P, P->Tx);
     if (!bad_rows.empty()) return fail(bad_rows);
   }
+  if (P->cg_pack) {  // and those of the coefficient gradient
+    const std::string bad_grad = check_tiling(*P, P->Tc);
+    if (!bad_grad.empty()) return fail(bad_grad);
+  }
   return SPINSUM_OK;
 }
+
 extern "C" void spinsum_plan_destroy(spinsum_plan_t P) {
   if (!P) return;
   if (P->sub) spinsum_plan_destroy(P->sub);
