@@ -1046,14 +1046,25 @@ static void choose_rows_tiling(spinsum_plan_s* P) {
         const int64_t wg = (X.lds_elems * esz + 15) / 16 * 16 + (int64_t)X.max_rep_cnt * 4;
         return std::max<int64_t>(1, P->lds_limit / std::max<int64_t>(1, wg));
       };
-      if (per_cu_of(Tx) < 4) {  // as for the direct-LDS tiles (apply_tile)
+      // packed as for the direct-LDS tiles (apply_tile), but only where every
+      // CU has many orbits: a packed item combines up to eight in turn, and
+      // with few of them its own time counts (13^4 FP64, one cube 21.9 us
+      // packed and 12.9 one orbit an item, 37 cubes, 1295 orbits, 25.6 and
+      // 22.4, 294 cubes 101 and 113)
+      const int64_t cus = P->num_cus;
+      const bool few = Tx.nitems < 20 * cus;
+      if (per_cu_of(Tx) < 4 && !few) {
         t.item_tiles = Tx.max_orbit_tiles;
         Tiling packed;
         if (build_tiling(*P, P->n, P->ncubes, t, vmax, &packed) == SPINSUM_OK && packed.fits)
           Tx = std::move(packed);
       }
+      // (4D orbits of 256 elements that fill the slots of a CU: 256 threads,
+      // 15^4 FP64, 2905 orbits, 38.5 us against 40.1 with 512)
       const int64_t per_cu = per_cu_of(Tx);
-      P->x_threads = per_cu >= 4 ? 256 : per_cu >= 2 ? 512 : 1024;
+      P->x_threads = per_cu >= 4 || (P->d == 4 && few && Tx.nitems >= 4 * cus) ? 256
+                     : per_cu >= 2                                           ? 512
+                                                                             : 1024;
       Tx.nts = (P->flags & SPINSUM_FLAG_NT_STORES) ? 1 : 0;
       P->Tx = std::move(Tx);
       P->x_own = true;
