@@ -1036,6 +1036,13 @@ static void choose_rows_tiling(spinsum_plan_s* P) {
       // against 2.06 TB/s; 17^4, 1.5 times as much, 1.91 against 1.69)
       auto cover = [&](int b) { return ipow((P->n + b - 1) / b * b, P->d); };
       if (esz == 8 && cover(bl) * 5 > cover(P->T.g.bl) * 8) return;
+      // as do short rows: 4D, of part sectors at the same edge (FP64 runs
+      // of 3, 48 bytes: 9^4 1140 against 1186 us), and of an edge narrower by
+      // a third that does not cover an eighth less (FP32 runs of 3, 4^3
+      // against 6^3: 29^3 1.18 times as long, 33^3 1.07, 41^3 1.10; covering
+      // less, 31^3 0.83, 27^3 0.92, 37^3 0.96)
+      if (P->d == 4 && bl == P->T.g.bl && row < 64) return;
+      if (bl * 3 <= P->T.g.bl * 2 && cover(bl) * 8 > cover(P->T.g.bl) * 7) return;
       spinsum_tile_t t{};
       t.bl = bl;
       t.cubes_per_wg = 1;

@@ -51,6 +51,18 @@ def test_orbits_of_odd_rows_are_packed_where_there_are_many(tiles, n, inner, dty
     assert items < orbits * cubes if packed else items == orbits * cubes
 
 
+
+@pytest.mark.parametrize("d,n,inner,dtype,edge", [
+    (4, 9, 3, "f64", 0), (4, 11, 3, "f64", 0), (4, 9, 5, "f64", 2), (4, 9, 3, "f32", 4),
+    (3, 29, 3, "f32", 0), (3, 33, 3, "f32", 0), (3, 41, 3, "f32", 0), (3, 27, 3, "f32", 4),
+    (3, 31, 3, "f32", 4), (3, 37, 3, "f32", 4), (3, 33, 5, "f32", 4), (3, 33, 3, "f64", 6),
+    (3, 33, 1, "f32", 8), (3, 34, 1, "f32", 8), (3, 33, 1, "f64", 8)])
+def test_short_rows_stay_on_the_register_path(tiles, d, n, inner, dtype, edge):
+    """4D rows of part sectors at the register path's edge, and edges a third
+    narrower that do not cover an eighth less: its tiles stay."""
+    assert tiles(d, n, inner, dtype, True, 600)[0] == edge
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,dtype", [((150, 13, 13, 13, 13), "f64"), ((40, 13, 13, 13, 13), "f64"),
                                          ((200, 15, 15, 15, 15, 2), "f32")])
