@@ -995,7 +995,11 @@ static void choose_wide_tiling(spinsum_plan_s* P) {
   if (build_tiling(*P, P->n, P->ncubes, t, vmax, &Tx) != SPINSUM_OK || !Tx.fits ||
       (int64_t)Tx.vw * elem_size(*P) != 16)
     return;
-  Tx.nts = choose_nts(*P, Tx, (int64_t)Tx.orbits.size());
+  // the store mode of the 8^3 tiles: these cover as much of a cube, and the
+  // longer rows are still parts of lines (70^3 in place, 128 MB again and
+  // again, in the Infinity Cache, cached 45 us, non-temporal 61; 1 GB 505 and
+  // 516)
+  Tx.nts = T.nts;
   Tx.ntl = choose_ntl(*P, Tx);
   P->Tx = std::move(Tx);
   P->x_own = true;

@@ -63,6 +63,15 @@ def test_short_rows_stay_on_the_register_path(tiles, d, n, inner, dtype, edge):
     assert tiles(d, n, inner, dtype, True, 600)[0] == edge
 
 
+@pytest.mark.parametrize("n,dtype,edge", [(30, "f64", 10), (46, "f64", 10), (70, "f64", 10),
+                                          (78, "f64", 10), (90, "f64", 10), (36, "f32", 12),
+                                          (108, "f32", 12)])
+def test_wide_tiles_store_as_the_plans_tiles(tiles, n, dtype, edge):
+    for inplace in (False, True):
+        bl, _, _, nts, plan_nts = tiles(3, n, 1, dtype, inplace, 100)
+        assert (bl, nts) == (edge, plan_nts)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,dtype", [((150, 13, 13, 13, 13), "f64"), ((40, 13, 13, 13, 13), "f64"),
                                          ((200, 15, 15, 15, 15, 2), "f32")])
