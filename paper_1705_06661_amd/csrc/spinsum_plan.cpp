@@ -939,9 +939,20 @@ bool cube_persistent(const spinsum_plan_s& P, const Tiling& T) {
 // against 5.53 on 40^2.  (Tiles of whole lines are as good: 12^3 with inner
 // runs of 8, 6.08 against 5.99; so are 16^3 FP32 tiles, two orbits an item,
 // on 32^3: 4.83 against 4.65.)
+// Tiles of whole 64-byte sectors stay where the Infinity Cache (256 MB) holds
+// the tensor but not with room to spare: k_cube's non-temporal loads pass it
+// by.  24^3 FP64 in place, the same tensor again and again / tensors in turn,
+// tiles and cubes, us: 128 MB 38 49 / 60 50, 192 MB 53 76 / 82 75, 256 MB 69
+// 97 / 99 96, 384 MB 153 142 / 156 142; 120^2 the same.  FP32 orbits have
+// twice the arithmetic per byte and gain from 1 GB on alone (24^3 with runs of
+// 2 in place: 128 MB 45 63 / 62 63, 512 MB 203 213 / 203 215, 1 GB 433 411).
 static void choose_cube_tiling(spinsum_plan_s* P) {
   const Tiling& T = P->T;
   const int esz = elem_size(*P);
+  const int64_t bytes = P->elems * esz, mb = (int64_t)1 << 20;
+  const bool sectors = ((int64_t)T.g.bl * P->inner * esz) % 64 == 0 &&
+                       ((int64_t)P->n * P->inner * esz) % 64 == 0;
+  if (sectors && (esz == 8 ? bytes > 128 * mb && bytes <= 256 * mb : bytes <= 512 * mb)) return;
   if (P->x_own || P->pair || P->batched || P->d > 3 || P->ncubes <= 0 || P->n <= 0 ||
       T.g.bl >= P->n || P->tile.variant != SPINSUM_VARIANT_DIRECT_LDS || P->tile.item_tiles != 0 ||
       ((int64_t)T.g.bl * P->inner * esz) % 128 == 0 ||

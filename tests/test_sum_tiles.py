@@ -72,6 +72,17 @@ def test_wide_tiles_store_as_the_plans_tiles(tiles, n, dtype, edge):
         assert (bl, nts) == (edge, plan_nts)
 
 
+@pytest.mark.parametrize("d,n,inner,dtype,cubes,edge", [
+    (3, 24, 1, "f64", 1213, 24), (3, 24, 1, "f64", 1214, 0), (3, 24, 1, "f64", 2427, 0),
+    (3, 24, 1, "f64", 2428, 24), (2, 120, 1, "f64", 1165, 120), (2, 120, 1, "f64", 2000, 0),
+    (2, 120, 1, "f64", 2400, 120), (3, 24, 2, "f32", 600, 0), (3, 24, 2, "f32", 4854, 0),
+    (3, 24, 2, "f32", 4855, 24), (3, 16, 5, "f32", 1638, 16), (3, 16, 5, "f32", 3000, 16)])
+def test_tiles_where_the_infinity_cache_holds_the_tensor(tiles, d, n, inner, dtype, cubes, edge):
+    """Whole cubes in place of tiles of whole sectors: not for 128 to 256 MB
+    in FP64, up to 512 MB in FP32 (tiles of part sectors: at every size)."""
+    assert tiles(d, n, inner, dtype, True, cubes)[0] == edge
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,dtype", [((150, 13, 13, 13, 13), "f64"), ((40, 13, 13, 13, 13), "f64"),
                                          ((200, 15, 15, 15, 15, 2), "f32")])
