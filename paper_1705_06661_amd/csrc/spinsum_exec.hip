@@ -629,8 +629,11 @@ extern "C" spinsum_status spinsum_adjoint_coef_grad(spinsum_plan_t P, const void
   // the whole group (d <= 3: a 4D orbit's 48 values and 24 sums leave no
   // registers for the product): 28^3 FP64 1103 us in two launches, 793 in
   // one; on the gradient's own ragged tiles of 22^3, whole for the adjoint
-  // alone, 957 and 818, of 26^3 1076 and 916
-  if (P->elems != 0 && P->d <= 3 && P->sub == nullptr &&
+  // alone, 957 and 818, of 26^3 1076 and 916; not on large 2D tiles of both
+  // tensors, two workgroups a CU (128^2 FP32 1.33 times as long in one
+  // launch, 140^2 1.57, 160^2 1.54)
+  const bool own_pair = P->cg_pack && !P->cg_own_split && P->T.g.bl == P->T.g.n;
+  if (P->elems != 0 && P->d <= 3 && P->sub == nullptr && !(P->d == 2 && own_pair) &&
       !(P->flags & (SPINSUM_FLAG_CHAIN_STAGES | SPINSUM_FLAG_MULTI_PASS)))
     return coef_grad_impl(P, x, g, grad, false, stream, gx);
   st = coef_grad_impl(P, x, g, grad, false, stream);  // (first: gx may be g)

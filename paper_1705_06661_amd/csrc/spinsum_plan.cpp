@@ -674,8 +674,11 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
     // it takes them (22^3 FP64 3.69 against 2.46 TB/s with both tensors'
     // tiles in LDS, 24^3 4.62 against 3.14, 26^3 3.15 against 2.01, 100^2
     // 4.95 against 2.51).  Cubes that fit stay whole (20^3 3.93 against 3.09).
+    // Not in 2D FP32, where whole chunks leave 16^2: both tensors' large
+    // tiles serve better (the gradient alone, 128 MB a tensor or more: 128^2
+    // 1.57 times as long in 16^2 tiles, 140^2 1.12, 148^2 1.34, 160^2 1.25).
     for (int bl : {P->d == 2 ? 22 : 8, P->d == 2 ? 16 : 4}) {
-      if (bl >= P->n || ((int64_t)bl * esz) % 16 != 0) continue;
+      if (bl >= P->n || ((int64_t)bl * esz) % 16 != 0 || (P->d == 2 && esz == 4)) continue;
       spinsum_tile_t t = P->tile;
       t.bl = bl;
       t.cubes_per_wg = 1;
