@@ -99,6 +99,26 @@ spinsum_status prepare_kernel(spinsum_plan_s* P, const void* k, size_t shmem) {
   return SPINSUM_OK;
 }
 
+// A launch takes fewer than 2^32 threads (the runtime cuts a larger grid short
+// without an error), so larger ones go in several, each of whole eighths for
+// the XCDs.
+int64_t max_groups(int threads) { return 0xFFFFFFFFll / threads / 8 * 8; }
+
+// launch(c0, n) over ranges of the ncubes cubes, in order, each range within
+// one launch's threads.  A work item is `unit` cubes (items = 1) or a cube has
+// `items` of them (unit = 1); their order is free, so ranges are too.
+template <typename F>
+spinsum_status for_cubes(int64_t ncubes, int64_t unit, int64_t items, int threads, F launch) {
+  const int64_t most = max_groups(threads);
+  if (items > most) return SPINSUM_ERR_UNSUPPORTED;
+  const int64_t step = most / std::max<int64_t>(1, items) * unit;
+  for (int64_t c0 = 0; c0 < ncubes; c0 += step) {
+    const spinsum_status st = launch(c0, std::min(step, ncubes - c0));
+    if (st != SPINSUM_OK) return st;
+  }
+  return SPINSUM_OK;
+}
+
 // Kernel, dynamic LDS and workgroup size of a plan's exec / adjoint launch
 // (both launch the same kernel), and whether that kernel is persistent.
 struct LaunchCfg {
@@ -231,24 +251,30 @@ spinsum_status launch_exec(spinsum_plan_s* P, const void* in, void* out, hipStre
   a.nreps = (int32_t)Tl.reps.size();
   spinsum_status st = prepare_kernel(P, c.k, c.shmem);
   if (st != SPINSUM_OK) return st;
-  int64_t grid;
-  if (c.kind == kKindCube) {  // one persistent workgroup per CU
-    a.xcd_per = (Tl.nitems + 7) / 8;
-    grid = std::max<int64_t>(8, (int64_t)P->num_cus / 8 * 8);
-  } else if (c.persistent) {
-    grid = persistent_grid(P, Tl.nitems);
-    a.xcd_per = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) ? 0 : (Tl.nitems + 7) / 8;
-  } else if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {
-    a.xcd_per = 0;
-    grid = Tl.nitems;
-  } else {
-    a.xcd_per = (Tl.nitems + 7) / 8;
-    grid = a.xcd_per * 8;
+  if (c.kind == kKindCube || c.persistent) {
+    // kKindCube: one persistent workgroup per CU
+    const int64_t grid = c.persistent ? persistent_grid(P, Tl.nitems)
+                                      : std::max<int64_t>(8, (int64_t)P->num_cus / 8 * 8);
+    a.xcd_per = (c.persistent && (P->flags & SPINSUM_FLAG_NO_XCD_REMAP)) ? 0 : (Tl.nitems + 7) / 8;
+    void* kargs[] = {&a};
+    hipError_t e = hipLaunchKernel(c.k, dim3((unsigned)grid), dim3(c.threads), kargs, c.shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
   }
-  void* kargs[] = {&a};
-  hipError_t e = hipLaunchKernel(c.k, dim3((unsigned)grid), dim3(c.threads), kargs, c.shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
-  return SPINSUM_OK;
+  const bool whole = Tl.g.bl == Tl.g.n;
+  const int64_t unit = whole ? Tl.g.cpw : 1, items = whole ? 1 : Tl.g.ngroups;
+  return for_cubes(Tl.g.ncubes, unit, items, c.threads, [&](int64_t c0, int64_t n) {
+    ExecArgs<T> b = a;
+    b.in += c0 * Tl.g.cube_elems;
+    b.out += c0 * Tl.g.cube_elems;
+    b.g.ncubes = n;
+    b.nitems = (n + unit - 1) / unit * items;
+    const bool plain = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) != 0;
+    b.xcd_per = plain ? 0 : (b.nitems + 7) / 8;
+    const int64_t grid = plain ? b.nitems : b.xcd_per * 8;
+    void* kargs[] = {&b};
+    hipError_t e = hipLaunchKernel(c.k, dim3((unsigned)grid), dim3(c.threads), kargs, c.shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
+  });
 }
 
 // Index-pair form: one tile orbit of one pair block per workgroup.
@@ -278,18 +304,30 @@ spinsum_status launch_pair(spinsum_plan_s* P, const void* in, void* out, hipStre
   const size_t shmem = (size_t)a.lds_tile_bytes + (size_t)Tl.max_rep_cnt * 4;
   spinsum_status st = prepare_kernel(P, k, shmem);
   if (st != SPINSUM_OK) return st;
-  int64_t grid;
-  if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {
-    a.xcd_per = 0;
-    grid = Tl.nitems;
-  } else {
-    a.xcd_per = (Tl.nitems + 7) / 8;
-    grid = a.xcd_per * 8;
-  }
-  void* kargs[] = {&a};
-  hipError_t e =
-      hipLaunchKernel(k, dim3((unsigned)grid), dim3(P->tile.threads), kargs, shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
+  // `norb` orbits from `orbits` on, of n pair blocks from block c0 on
+  auto launch = [&](int64_t c0, int64_t n, int64_t o0, int64_t norb) {
+    PairArgs<T> b = a;
+    b.in += c0 * Tl.g.cube_elems;
+    b.out += c0 * Tl.g.cube_elems;
+    b.orbits += o0;
+    b.nitems = n * norb;
+    const bool plain = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) != 0;
+    b.xcd_per = plain ? 0 : (b.nitems + 7) / 8;
+    const int64_t grid = plain ? b.nitems : b.xcd_per * 8;
+    void* kargs[] = {&b};
+    hipError_t e =
+        hipLaunchKernel(k, dim3((unsigned)grid), dim3(P->tile.threads), kargs, shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
+  };
+  const int64_t most = max_groups(P->tile.threads), norb = P->pg.norb;
+  if (norb <= most)
+    return for_cubes(P->ncubes, 1, norb, P->tile.threads,
+                     [&](int64_t c0, int64_t n) { return launch(c0, n, 0, norb); });
+  for (int64_t c0 = 0; c0 < P->ncubes; ++c0)  // a block's orbits in several launches
+    for (int64_t o0 = 0; o0 < norb; o0 += most) {
+      st = launch(c0, 1, o0, std::min(most, norb - o0));
+      if (st != SPINSUM_OK) return st;
+    }
   return SPINSUM_OK;
 }
 
@@ -314,20 +352,18 @@ spinsum_status launch_batched(spinsum_plan_s* P, const void* const* in, void* co
   const size_t shmem = c.shmem;
   spinsum_status st = prepare_kernel(P, k, shmem);
   if (st != SPINSUM_OK) return st;
-  int64_t grid;
-  if (c.persistent) {
-    grid = persistent_grid(P, a.nitems);
-    a.xcd_per = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) ? 0 : (a.nitems + 7) / 8;
-  } else if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {
-    a.xcd_per = 0;
-    grid = a.nitems;
-  } else {
-    a.xcd_per = (a.nitems + 7) / 8;
-    grid = a.xcd_per * 8;
+  const bool plain = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) != 0;
+  // (one range for the persistent launch, whose grid is small)
+  const int64_t most = c.persistent ? a.nitems : max_groups(c.threads), total = a.nitems;
+  for (int64_t i0 = 0; i0 < total; i0 += most) {
+    a.items = reinterpret_cast<const BatchItem*>(P->d_items) + i0;
+    a.nitems = std::min(most, total - i0);
+    a.xcd_per = plain ? 0 : (a.nitems + 7) / 8;
+    const int64_t grid = c.persistent ? persistent_grid(P, a.nitems) : plain ? a.nitems : a.xcd_per * 8;
+    void* kargs[] = {&a};
+    hipError_t e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(kThreads), kargs, shmem, stream);
+    if (e != hipSuccess) return hip_error(P, e);
   }
-  void* kargs[] = {&a};
-  hipError_t e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(kThreads), kargs, shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
   return SPINSUM_OK;
 }
 
@@ -517,17 +553,23 @@ spinsum_status launch_cgrad(spinsum_plan_s* P, const void* x, const void* g, voi
   hipLaunchKernelGGL(k_zero_f64, dim3(64), dim3(kThreads), 0, stream, a.grad, kGradSlots * df);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(P, e);
-  int64_t grid;
-  if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {
-    a.xcd_per = 0;
-    grid = Tl.nitems;
-  } else {
-    a.xcd_per = (Tl.nitems + 7) / 8;
-    grid = a.xcd_per * 8;
-  }
-  void* kargs[] = {&a};
-  e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(threads), kargs, shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
+  const bool whole = Tl.g.bl == Tl.g.n;
+  const int64_t unit = whole ? Tl.g.cpw : 1, items = whole ? 1 : Tl.g.ngroups;
+  st = for_cubes(Tl.g.ncubes, unit, items, threads, [&](int64_t c0, int64_t n) {
+    CGradArgs<T> b = a;
+    b.x += c0 * Tl.g.cube_elems;
+    b.gr += c0 * Tl.g.cube_elems;
+    if (adj) b.gx += c0 * Tl.g.cube_elems;
+    b.g.ncubes = n;
+    b.nitems = (n + unit - 1) / unit * items;
+    const bool plain = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) != 0;
+    b.xcd_per = plain ? 0 : (b.nitems + 7) / 8;
+    const int64_t grid = plain ? b.nitems : b.xcd_per * 8;
+    void* kargs[] = {&b};
+    hipError_t el = hipLaunchKernel(k, dim3((unsigned)grid), dim3(threads), kargs, shmem, stream);
+    return el == hipSuccess ? SPINSUM_OK : hip_error(P, el);
+  });
+  if (st != SPINSUM_OK) return st;
   hipLaunchKernelGGL(k_grad_reduce, dim3(df), dim3(kThreads), 0, stream,
                      (const double*)a.grad, grad, df);
   e = hipGetLastError();
@@ -741,7 +783,7 @@ spinsum_status launch_pack(spinsum_plan_s* P, const void* full, void* packed, bo
       (size_t)a.lds_tile_bytes + (persist ? (size_t)0 : (size_t)Tl.max_rep_cnt * 4);
   spinsum_status st = prepare_kernel(P, k, shmem);
   if (st != SPINSUM_OK) return st;
-  int64_t grid;
+  const int threads = own ? P->pk_threads : P->tile.threads;
   if (persist) {
     a.xcd_per = (P->ncubes + 7) / 8;
     const int nt = (int)Tl.groups.size();
@@ -756,19 +798,31 @@ spinsum_status launch_pack(spinsum_plan_s* P, const void* full, void* packed, bo
       const int64_t w8 = std::min<int64_t>(std::max<int64_t>(1, share), a.xcd_per);
       a.tmpl_wg[t + 1] = a.tmpl_wg[t] + (int32_t)(8 * w8);
     }
-    grid = a.tmpl_wg[nt];
-  } else if (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) {
-    a.xcd_per = 0;
-    grid = Tl.nitems;
-  } else {
-    a.xcd_per = (Tl.nitems + 7) / 8;
-    grid = a.xcd_per * 8;
+    void* kargs[] = {&a};
+    hipError_t e = hipLaunchKernel(k, dim3((unsigned)a.tmpl_wg[nt]), dim3(threads), kargs, shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
   }
-  void* kargs[] = {&a};
-  hipError_t e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(own ? P->pk_threads : P->tile.threads),
-                                 kargs, shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
-  return SPINSUM_OK;
+  const bool whole = Tl.g.bl == Tl.g.n;
+  const int64_t unit = whole ? Tl.g.cpw : 1, items = whole ? 1 : Tl.g.ngroups;
+  return for_cubes(Tl.g.ncubes, unit, items, threads, [&](int64_t c0, int64_t n) {
+    PackArgs<T> b = a;
+    const int64_t f0 = c0 * Tl.g.cube_elems, p0 = c0 * a.ncomb * P->inner;
+    if (pack) {
+      b.full_in += f0;
+      b.packed_out += p0;
+    } else {
+      b.full_out += f0;
+      b.packed_in += p0;
+    }
+    b.g.ncubes = n;
+    b.nitems = (n + unit - 1) / unit * items;
+    const bool plain = (P->flags & SPINSUM_FLAG_NO_XCD_REMAP) != 0;
+    b.xcd_per = plain ? 0 : (b.nitems + 7) / 8;
+    const int64_t grid = plain ? b.nitems : b.xcd_per * 8;
+    void* kargs[] = {&b};
+    hipError_t e = hipLaunchKernel(k, dim3((unsigned)grid), dim3(threads), kargs, shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
+  });
 }
 
 // Unpacking by gather (k_unpack_gather).
@@ -825,14 +879,25 @@ spinsum_status launch_gather(spinsum_plan_s* P, const void* packed, const void* 
   const size_t shmem = (size_t)gather_lds_bytes(*P, a.cpi, nc, a.batch, persist);
   spinsum_status st = prepare_kernel(P, k, shmem);
   if (st != SPINSUM_OK) return st;
-  a.xcd_per = (a.nitems + 7) / 8;
-  // persistent: one workgroup per CU, one share per XCD
-  const int64_t resident = std::max<int64_t>(1, P->num_cus / 8);
-  const int64_t per_xcd = persist ? std::min<int64_t>(a.xcd_per, resident) : a.xcd_per;
-  void* kargs[] = {&a};
-  hipError_t e = hipLaunchKernel(k, dim3((unsigned)(per_xcd * 8)), dim3(P->pg_threads), kargs, shmem, stream);
-  if (e != hipSuccess) return hip_error(P, e);
-  return SPINSUM_OK;
+  if (persist) {  // one workgroup per CU, one share per XCD
+    a.xcd_per = (a.nitems + 7) / 8;
+    const int64_t per_xcd = std::min<int64_t>(a.xcd_per, std::max<int64_t>(1, P->num_cus / 8));
+    void* kargs[] = {&a};
+    hipError_t e = hipLaunchKernel(k, dim3((unsigned)(per_xcd * 8)), dim3(P->pg_threads), kargs, shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
+  }
+  return for_cubes(P->ncubes, 1, a.parts, P->pg_threads, [&](int64_t c0, int64_t n) {
+    GatherArgs<T> b = a;
+    b.packed += c0 * nc * P->inner;
+    b.full += c0 * a.cube_elems;
+    b.ncubes = n;
+    b.nitems = n * a.parts;
+    b.xcd_per = (b.nitems + 7) / 8;
+    void* kargs[] = {&b};
+    hipError_t e =
+        hipLaunchKernel(k, dim3((unsigned)(b.xcd_per * 8)), dim3(P->pg_threads), kargs, shmem, stream);
+    return e == hipSuccess ? SPINSUM_OK : hip_error(P, e);
+  });
 }
 
 spinsum_status pack_impl(spinsum_plan_s* P, const void* full, void* packed, bool pack,
@@ -959,11 +1024,12 @@ extern "C" spinsum_status spinsum_stream_copy(const void* in, void* out, int64_t
   if (nbytes == 0) return SPINSUM_OK;
   if (in == nullptr || out == nullptr) return SPINSUM_ERR_INVALID_ARG;
   if ((((uintptr_t)in) | ((uintptr_t)out)) & 15u) return SPINSUM_ERR_MISALIGNED;
-  const int64_t nvec = nbytes / 16;
-  const int64_t grid = (nvec + kThreads - 1) / kThreads;
-  if (grid >= (1ll << 31)) return SPINSUM_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(k_copy, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream,
-                     (const double*)in, (double*)out, nvec);
+  const int64_t most = max_groups(kThreads) * kThreads;  // vectors of one launch
+  for (int64_t v0 = 0; v0 < nbytes / 16; v0 += most) {
+    const int64_t nvec = std::min(most, nbytes / 16 - v0);
+    hipLaunchKernelGGL(k_copy, dim3((unsigned)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                       (hipStream_t)stream, (const double*)in + 2 * v0, (double*)out + 2 * v0, nvec);
+  }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SPINSUM_OK : SPINSUM_ERR_HIP;
 }
