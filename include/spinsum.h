@@ -157,10 +157,12 @@ typedef struct {
   int64_t batch_item_bytes; /* batched: whole-cube items are packed up to this size */
   int batch_persistent;  /* batched: 1 = persistent workgroups walk the item list,
                             0 = one workgroup per item */
-  int nt_stores;         /* 1: non-temporal stores (default where tile rows are at least
-                            64 bytes and a cube has at most 128 tile orbits, and for whole
-                            cubes); 0: cached stores, which let the L2 merge the partial
-                            128-byte lines that short rows or far-apart items write */
+  int nt_stores;         /* 1: non-temporal stores (default for whole cubes, and where tile
+                            rows are at least 64 bytes and a cube has at most 128 tile
+                            orbits); 0: cached stores, which let the L2 merge the partial
+                            128-byte lines that short rows or far-apart items write: also,
+                            out of place, where tile rows do not start and end on 64-byte
+                            sectors, and where items pack orbits of rows under 128 bytes */
   int exec_d;            /* axes of the group the kernels permute: d, or fewer where the
                             operator's permutations move a smaller run of axes (see
                             spinsum_plan); the tiling fields above describe that group */
@@ -199,9 +201,10 @@ typedef struct {
                             are not whole 16-byte chunks, tiles whose rows are loaded and
                             stored in 16-byte pieces at any element alignment; where they
                             are parts of 128-byte lines although a cube fits a CU's LDS (at
-                            least two cubes per CU, d <= 3), whole cubes.  0 where they run
-                            on the tile above (also after spinsum_plan_set_tile with a tile
-                            edge) */
+                            least two cubes per CU, d <= 3), whole cubes, unless the
+                            Infinity Cache holds the tensor; where 8^3 rows lie off 32-byte
+                            boundaries, 10^3 (FP64) or 12^3 (FP32).  0 where they run on the
+                            tile above (also after spinsum_plan_set_tile with a tile edge) */
   int unpack_gather;     /* spinsum_unpack forms every element where it is stored, from the
                             packed values of its cube in LDS (the unpack_ fields above then
                             describe the tiles it would otherwise run on): 1: one item per

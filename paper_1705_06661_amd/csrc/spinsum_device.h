@@ -56,7 +56,7 @@
 namespace spinsum {
 namespace {
 
-constexpr int kThreads = 256;     // workgroup size of every kernel but k_lds
+constexpr int kThreads = 256;     // workgroup size of k_exec, k_pipe, k_batched and k_cgrad_split
 constexpr int kMaxThreads = 1024; // k_lds, k_ldsp: 256, 512 or 1024 (blockDim.x)
 constexpr int kUnroll = 4;
 constexpr int kUnpackBatch = 4;   // k_unpack: packed values requested together per thread

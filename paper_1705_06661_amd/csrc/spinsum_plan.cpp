@@ -8,7 +8,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <cstdlib>
 #include <map>
 #include <numeric>
 #include <utility>

@@ -99,10 +99,11 @@ struct spinsum_plan_s {
   // (decided with the tables, upload_tables)
   bool cg_split = false;
   bool cg_own_split = false;  // Tc holds tiles for k_cgrad_split
-  // The sum's own tiling (x_own): where the plan's default tiles have no rows
-  // of whole 16-byte chunks, or part lines although a cube fits a CU, exec
-  // and adjoint run on these tiles instead of T (choose_rows_tiling, k_rows;
-  // choose_cube_tiling, k_cube)
+  // The sum's own tiling (x_own): exec and adjoint run on these tiles instead
+  // of T where the plan's default tiles have no rows of whole 16-byte chunks
+  // (choose_rows_tiling, k_rows), part lines although a cube fits a CU
+  // (choose_cube_tiling, k_cube), or rows off 32-byte boundaries
+  // (choose_wide_tiling)
   spinsum::Tiling Tx;
   bool x_own = false;
   int x_threads = 256;
