@@ -79,6 +79,10 @@ def kernel_name(info, dtype="double", chain=False):
     nts = "true" if info["nt_stores"] else "false"
     if info["pair_extent"] > 0:
         return f"k_pair<{dtype}, {d}, {c}, {nts}>"
+    if v == 1 and info["persistent_per_cu"]:  # whole cubes, persistent (8 or 10 chunks a thread)
+        return f"k_cube<{dtype}, {d}, {c}, *>"
+    if v == 3 and info["sum_bl"]:  # rows that are not whole 16-byte chunks
+        return f"k_rows<{dtype}, {d}, {c}, *>"
     if v == 1:
         return f"k_lds<{dtype}, {d}, {c}, {nts}>"
     if v == 4:
@@ -91,6 +95,21 @@ def kernel_name(info, dtype="double", chain=False):
 def batched_kernel_name(info):
     """The FP64 3D batched kernel (16-byte chunks), one-shot or persistent."""
     return "k_batched<double, 3, 2, %s>" % ("true" if info["batch_persistent"] else "false")
+
+
+def cgrad_kernel_name(info, adjoint):
+    """The FP64 3D kernel of the coefficient gradient, alone or with the
+    adjoint."""
+    return "%s<double, 3, %s>" % ("k_cgrad_split" if info["coef_grad_split"] else "k_cgrad",
+                                  "true" if adjoint else "false")
+
+
+def unpack_kernel_name(info):
+    """The FP64 3D unpacking kernel: by gather, or on tiles."""
+    if info["unpack_gather"]:
+        return "k_unpack_gather<double, 3, %s>" % ("true" if info["unpack_gather"] == 2 else "false")
+    return "%s<double, 3, %s>" % ("k_unpack_persist" if info["unpack_persistent"] else "k_unpack",
+                                  "true" if info["unpack_nt_stores"] else "false")
 
 
 def warm(fn, seconds=0.25, refill=None):
@@ -358,7 +377,7 @@ def accuracy_report(ss, workloads, dev, stream):
 PROFILE_FORMS = ("3d_v64_o32_inplace", "4d_v24_o12_inplace", "4d_table2_5_80_premultiplied",
                  "3d_pairs_v48_o24_inplace", "3d_v48_o24_forward_fp64", "3d_coef_grad",
                  "3d_unpack_antisymmetric", "3d_v48_o24_adjoint_fp64", "3d_v48_o24_forward_fp32",
-                 "batched_graph", "stream_copy")
+                 "3d_v40_o33_inplace", "3d_backward_v32_o16", "batched_graph", "stream_copy")
 
 
 def profile_one(name, steps, warmup):
@@ -423,6 +442,21 @@ def profile_one(name, steps, warmup):
         else:
             fn = lambda: ss.spinsum_exec(p, x, y, stream)
         nbytes = 2 * x.numel() * x.element_size()
+    elif name == "3d_v40_o33_inplace":
+        # an odd extent: rows that are not whole 16-byte chunks
+        x = workloads.uniform((40, 40, 4, 33, 33, 33), 6000, device=dev)
+        p = ss.spinsum_plan(x.shape, 3, 3, alpha, inplace=True)
+        fn = lambda: ss.spinsum_exec(p, x, x, stream)
+        nbytes = 2 * x.numel() * 8
+    elif name == "3d_backward_v32_o16":
+        # both gradients of a backward pass: two tensors read, one written
+        x = workloads.uniform((32, 32, 32, 16, 16, 16), 6100, device=dev)
+        g = workloads.uniform(x.shape, 6101, device=dev)
+        gx = torch.empty_like(g)
+        p = ss.spinsum_plan(x.shape, 3, 3, alpha)
+        fn = lambda: ss.spinsum_adjoint_coef_grad(p, x, g, gx, stream)
+        nbytes = 3 * x.numel() * 8
+        split = {"algorithmic_read_bytes": 2 * x.numel() * 8, "algorithmic_write_bytes": x.numel() * 8}
     elif name == "batched_graph":
         # the 200 power-law blocks, the autotuner's item size and launch
         # style, one graph launch per step (the tuning launches come first;
@@ -455,12 +489,10 @@ def profile_one(name, steps, warmup):
                       "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1),
                       "algorithmic_bytes_per_launch": nbytes,
                       "kernel": {"stream_copy": "k_copy",
-                                 "3d_coef_grad": ("k_cgrad_split<double, 3>" if info["coef_grad_split"]
-                                                  else "k_cgrad<double, 3>"),
+                                 "3d_coef_grad": cgrad_kernel_name(info, False),
+                                 "3d_backward_v32_o16": cgrad_kernel_name(info, True),
                                  "batched_graph": batched_kernel_name(info),
-                                 "3d_unpack_antisymmetric": "%s<double, 3, %s>" % (
-                                     "k_unpack_persist" if info["unpack_persistent"] else "k_unpack",
-                                     "true" if info["unpack_nt_stores"] else "false")}.get(
+                                 "3d_unpack_antisymmetric": unpack_kernel_name(info)}.get(
                           name, kernel_name(info, "float" if name.endswith("fp32") else "double")),
                       "tile_edge": info["bl"], "launches_timed": steps, **split,
                       "kernel_source_hash": kernel_source_hash()}), flush=True)
