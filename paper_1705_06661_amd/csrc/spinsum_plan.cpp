@@ -657,7 +657,8 @@ static bool cgrad_split_ok(const spinsum_plan_s& P, const Tiling& T) {
   return lds <= P.lds_limit;
 }
 
-static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits);
+static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits,
+                      bool unpack = false);
 
 static void build_cgrad_tiling(spinsum_plan_s* P) {
   const Tiling& T = P->T;
@@ -748,13 +749,18 @@ static void build_cgrad_tiling(spinsum_plan_s* P) {
 //  - where orbits are packed and rows are part lines: the items of a cube are
 //    few and write neighbouring parts together (32^3 FP32 in place 4.90
 //    against 5.21, out of place 4.68 and 5.29).
-static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits) {
+// Unpacking's own tiles have rows of 128 bytes and more and read nothing of the
+// tensor: part sectors are few, and non-temporal stores serve better (300^2
+// FP64, 256 MB 102 us against 147 cached, 3 GB 1487 and 1582).
+static int choose_nts(const spinsum_plan_s& P, const Tiling& T, int64_t orbits,
+                      bool unpack) {
   if (P.flags & SPINSUM_FLAG_NO_NT_STORES) return 0;
   if (P.flags & SPINSUM_FLAG_NT_STORES) return 1;
   const bool whole = (T.g.bl == T.g.n) && !P.pair;
   if (whole) return 1;
   const int64_t row = (int64_t)T.g.bl * T.g.inner * elem_size(P);
   const int64_t stride = (int64_t)T.g.n * T.g.inner * elem_size(P);
+  if (unpack) return (row >= 64 && orbits <= 128) ? 1 : 0;
   if (!P.inplace && T.g.bl < T.g.n && (row % 64 != 0 || stride % 64 != 0)) return 0;
   if (!P.pair && row < 128 && T.groups.size() < T.orbits.size()) return 0;
   return (row >= 64 && orbits <= 128) ? 1 : 0;
@@ -827,7 +833,7 @@ static void choose_unpack_tiling(spinsum_plan_s* P) {
     if (!Tu.fits || lds_of(Tu) > P->lds_limit) continue;
     if (bl < P->n && (int64_t)Tu.vw * esz != 16) continue;  // rows of whole 16-byte chunks
     const int64_t per_cu = std::max<int64_t>(1, P->lds_limit / std::max<int64_t>(1, lds_of(Tu)));
-    Tu.nts = choose_nts(*P, Tu, (int64_t)Tu.orbits.size());
+    Tu.nts = choose_nts(*P, Tu, (int64_t)Tu.orbits.size(), true);
     P->pk_threads = per_cu >= 4 ? 256 : per_cu >= 2 ? 512 : 1024;
     P->Tu = std::move(Tu);
     P->pk_own = true;

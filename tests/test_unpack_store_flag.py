@@ -41,3 +41,16 @@ def test_unpacking_with_the_flag(shape, d, dtype, mode):
         outs.append(ss.spinsum_unpack(p, pk, torch.empty(shape, dtype=dtype, device=pk.device)))
     torch.cuda.synchronize()
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("shape,d,dtype,nt", [
+    ((400, 300, 300), 2, torch.float64, 1), ((400, 250, 250), 2, torch.float64, 1),
+    ((100, 500, 500), 2, torch.float64, 1), ((100, 300, 300, 3), 2, torch.float32, 1),
+    ((600, 54, 54, 54), 3, torch.float64, 0),  # the plan's own 8^3 tiles
+])
+def test_store_mode_of_unpackings_own_tiles(shape, d, dtype, nt):
+    """Unpacking on large tiles of its own stores non-temporally also where
+    rows are off 64-byte sectors; on the plan's tiles as the plan does."""
+    info = ss.spinsum_plan(shape, 1, d, [workloads.antisymmetrizer(d)], dtype=dtype,
+                           flags=ss.SPINSUM_FLAG_HOST_ONLY).info()
+    assert (info["unpack_gather"], info["unpack_nt_stores"]) == (0, nt)
